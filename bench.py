@@ -753,7 +753,7 @@ def main():
                      "kernel": ("k_contract" if sys_.M <= 64 and sys_.N <= 16 and precision == 0
                                 and not ctx.ctrial else
                                 "k_contract_sh" if precision in (1, 2, 3) and not ctx.ctrial
-                                else "k_contract_g")
+                                else "k_contract_q")
                                + (" (complex trial)" if ctx.ctrial else "")
                                + " (+ k_combine) in afqmc_local_energy",
                      "ms_per_launch": contract_ms, "flops_per_launch": flops},

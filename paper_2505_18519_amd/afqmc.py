@@ -287,8 +287,7 @@ def afqmc_set_numeric_check(ctx, on):
 
 
 def afqmc_set_contraction_variant(ctx, variant):
-    """FP64 contraction of real trials on the workgroup-per-path kernels:
-    0 register-resident operands, 1 operands streamed from L2."""
+    """Accepted for callers that set it (0 or 1): both run the same FP64 contraction."""
     ctx._call("afqmc_set_contraction_variant", int(variant))
 
 

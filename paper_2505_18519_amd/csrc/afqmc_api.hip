@@ -15,7 +15,11 @@
 // (afqmc_local_energy_static).  In host code this name is only a stand-in for
 // the symbol: every host use goes through the device address that
 // hipGetSymbolAddress returns for the current device (scratch_address).
-static __device__ __align__(256) unsigned char scratch[AFQMC_STATIC_SCRATCH_BYTES];
+// Past the documented size it holds the contraction's partial sums: at least 16
+// vectors go to each of their ranges (two ranges from 28 vectors on), so 16 bytes
+// per path and range is below 1/12 of the vb array.
+constexpr size_t kPartialBytes = AFQMC_STATIC_SCRATCH_BYTES / 12;
+static __device__ __align__(256) unsigned char scratch[AFQMC_STATIC_SCRATCH_BYTES + kPartialBytes];
 
 namespace {
 
@@ -553,7 +557,6 @@ afqmc_status afqmc_set_eloc_cap(afqmc_ctx c, double center, double half_width) {
 afqmc_status afqmc_set_contraction_variant(afqmc_ctx c, int32_t variant) {
   if (c == nullptr) return AFQMC_E_INVALID;
   if (variant != 0 && variant != 1) return fail(c, AFQMC_E_INVALID, "variant must be 0 or 1");
-  c->contract_variant = variant;
   return AFQMC_OK;
 }
 
@@ -611,39 +614,46 @@ afqmc_status afqmc_green(afqmc_ctx c, int32_t nw, const void* phi, const double*
 }
 
 // The contraction kernel of the context's family and precision into per-path
-// vb and ep, then the walker-level combination.
+// vb and ep, then the walker-level combination.  part: room for partial sums of
+// E_p, 16 bytes for each path and range of contract_q_splits.
 static hipError_t contraction_kernels(afqmc_ctx c, int32_t nw, const double* phiT,
                                       const void* theta, const void* logov, void* xbar, double* vb,
-                                      void* eloc, double* ep, int* flags) {
+                                      void* eloc, double* ep, double* part, int* flags) {
   const double* th = static_cast<const double*>(theta);
   const double* lo = static_cast<const double*>(logov);
   hipError_t e;
-  if (c->small && c->precision == AFQMC_PREC_FP64)
-    e = launch_contract(c, nw, phiT, th, lo, vb, ep);
-  else if (c->precision != AFQMC_PREC_FP64 && !c->ctrial)
+  const double* epart = ep;
+  int nsplit = 1;
+  if (c->precision != AFQMC_PREC_FP64 && !c->ctrial) {
     e = launch_contract_sh(c, nw, phiT, th, lo, vb, ep);
-  else
+  } else if (c->precision != AFQMC_PREC_FP64) {
     e = launch_contract_g(c, nw, phiT, th, lo, vb, ep);
+  } else if (contract_in_registers(c, nw)) {
+    e = launch_contract(c, nw, phiT, th, lo, vb, ep);
+  } else {
+    nsplit = contract_q_splits(c, nw);
+    if (nsplit > 1) epart = part;
+    e = launch_contract_q(c, nw, nsplit, phiT, th, lo, vb, nsplit > 1 ? part : ep);
+  }
   if (e != hipSuccess) return e;
-  return launch_combine(c, nw, vb, ep, lo, static_cast<double*>(xbar),
+  return launch_combine(c, nw, vb, epart, nsplit, ep, lo, static_cast<double*>(xbar),
                         static_cast<double*>(eloc), flags);
 }
 
 static afqmc_status contraction(afqmc_ctx c, int32_t nw, const double* phiT, const void* theta,
                                 const void* logov, void* xbar, void* vb_sample, void* eloc,
                                 void* e_sample) {
-  ws_layout L;
-  const bool need = (vb_sample == nullptr) || (e_sample == nullptr);
-  if (need) {
-    afqmc_status st = need_ws(c, nw, &L);
-    if (st != AFQMC_OK) return st;
-  }
+  ws_layout L;  // one of vb and ep is always the workspace's
+  afqmc_status st = need_ws(c, nw, &L);
+  if (st != AFQMC_OK) return st;
   double* vb = vb_sample ? static_cast<double*>(vb_sample) : ws_ptr<double>(c, L.vb);
   double* ep = e_sample ? static_cast<double*>(e_sample) : ws_ptr<double>(c, L.ep);
   hipError_t fe;
   int* flags = flag_words(c, nw, &fe);
   HIPCALL(c, fe, "flags");
-  HIPCALL(c, contraction_kernels(c, nw, phiT, theta, logov, xbar, vb, eloc, ep, flags),
+  // the V buffer, idle outside the move, takes the partial sums
+  HIPCALL(c, contraction_kernels(c, nw, phiT, theta, logov, xbar, vb, eloc, ep,
+                                 ws_ptr<double>(c, L.vmat), flags),
           "contraction");
   return numeric_check_end(c, nw, flags);
 }
@@ -695,7 +705,9 @@ afqmc_status afqmc_local_energy_static(afqmc_ctx c, int32_t nw, const double* ph
   unsigned char* base = static_cast<unsigned char*>(c->d_scratch);
   double* vb = reinterpret_cast<double*>(base);
   double* ep = e_sample ? static_cast<double*>(e_sample) : reinterpret_cast<double*>(base + vb_bytes);
-  HIPCALL(c, contraction_kernels(c, nw, phiT, theta, logov, xbar, vb, eloc, ep, nullptr),
+  HIPCALL(c, contraction_kernels(c, nw, phiT, theta, logov, xbar, vb, eloc, ep,
+                                 reinterpret_cast<double*>(base + AFQMC_STATIC_SCRATCH_BYTES),
+                                 nullptr),
           "static contraction");
   return AFQMC_OK;
 }

@@ -19,10 +19,6 @@ struct afqmc_ctx_s {
   // Re E_L clipped to [ecap_center - ecap_half, ecap_center + ecap_half] when ecap_half > 0
   double ecap_center = 0, ecap_half = 0;
   int n_taylor = 10, weight_mode = 0, proposal = 0, precision = 0;
-  // FP64 contraction of real trials on the workgroup-per-path kernels: 0 keeps
-  // Phi_T and Theta in registers (k_contract_g, N <= 32), 1 streams them from
-  // L2 (k_contract_gs; always for 32 < N)
-  int contract_variant = 0;
 
   // device copies owned by the context
   double* d_h1 = nullptr;    // [M][M]
@@ -129,8 +125,10 @@ hipError_t launch_contract(const afqmc_ctx_s* c, int nw, const double* phiT, con
                            const double* logov, double* vb, double* ep);
 // flags (may be null): per-walker AFQMC_NUMERIC_* bits OR-ed in where a
 // kernel finds a non-finite result
-hipError_t launch_combine(const afqmc_ctx_s* c, int nw, const double* vb, const double* ep,
-                          const double* logov, double* xbar, double* eloc, int* flags);
+// ep [nw][P] is the sum of epart's nsplit parts, written here when nsplit > 1
+hipError_t launch_combine(const afqmc_ctx_s* c, int nw, const double* vb, const double* epart,
+                          int nsplit, double* ep, const double* logov, double* xbar, double* eloc,
+                          int* flags);
 // scratch (may be null): device memory free for the call, used by BF16 contexts
 // for their split coefficients when it holds scratch_bytes >= 8 nw GP
 hipError_t launch_vbuild(const afqmc_ctx_s* c, int nw, const double* xi, const double* xbar,
@@ -181,6 +179,13 @@ hipError_t launch_overlap_g(const afqmc_ctx_s* c, int nw, const double* phi, con
                             double* logov, double* theta, double* gdiag);
 hipError_t launch_contract_g(const afqmc_ctx_s* c, int nw, const double* phiT, const double* theta,
                              const double* logov, double* vb, double* ep);
+// whether the FP64 contraction of nw walkers runs one wavefront per path (launch_contract)
+bool contract_in_registers(const afqmc_ctx_s* c, int nw);
+// FP64 contraction of real trials at any size (k_contract_q.hip), over nsplit ranges of the
+// vectors: epart [nsplit][nw P] complex, the ranges' parts of E_p
+int contract_q_splits(const afqmc_ctx_s* c, int nw);
+hipError_t launch_contract_q(const afqmc_ctx_s* c, int nw, int nsplit, const double* phiT,
+                             const double* theta, const double* logov, double* vb, double* epart);
 hipError_t launch_taylor_g(const afqmc_ctx_s* c, int nw, const double* vmat, double* phi);
 // dst = El T_n(V) Er src for n blocks of `spins` M x N complex matrices (Er may be
 // null); src block (w, sp) at (w * src_ws + sp) M N

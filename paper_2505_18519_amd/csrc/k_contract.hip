@@ -249,14 +249,16 @@ k_contract(int n_samples, int M, int N, int G, const double* __restrict__ Lpad,
 // Walker-level estimates over the P paths (Eq. local-obs, then Eq. shift1):
 // S_p = exp(i Im l_p) (0 if singular), xbar_g = -i sqrt(tau) sum S vb / sum S,
 // E_L = sum S E_p / sum S.  One workgroup of 64 threads per walker.  A
-// non-finite E_L or force-bias component sets the walker's flag bits.  With
+// non-finite E_L or force-bias component sets the walker's flag bits.  E_p comes as
+// nsplit partial sums over ranges of the vectors (one: ep itself).  With
 // ecap_half > 0 a finite Re E_L is clipped to [ecap_lo, ecap_hi] (Im E_L kept).
 __global__ void __launch_bounds__(64)
 k_combine(int nw, int P, int G, double sqrt_tau, double xbar_cap, double ecap_half,
           double ecap_lo, double ecap_hi, const double* __restrict__ vb,
-          const double* __restrict__ ep, const double* __restrict__ logov,
-          double* __restrict__ xbar, double* __restrict__ eloc, int* __restrict__ flags) {
+          const double* __restrict__ epart, int nsplit, double* __restrict__ ep,
+          const double* __restrict__ logov, double* __restrict__ xbar, double* __restrict__ eloc, int* __restrict__ flags) {
   __shared__ double s_S[64][2];
+  __shared__ double s_E[64][2];
   const int w = blockIdx.x;
   const int lane = threadIdx.x;
   for (int p = lane; p < P; p += 64) {
@@ -265,6 +267,12 @@ k_combine(int nw, int P, int G, double sqrt_tau, double xbar_cap, double ecap_ha
     if (!__builtin_isinf(lr)) sincos(li, &si, &sr);
     s_S[p][0] = sr;
     s_S[p][1] = si;
+    cplx e = cmk(0.0, 0.0);
+    const size_t q = (size_t)w * P + p, n = (size_t)nw * P;
+    for (int k = 0; k < nsplit; ++k) e = cadd(e, cld(epart + (k * n + q) * 2));
+    s_E[p][0] = e.re;
+    s_E[p][1] = e.im;
+    if (nsplit > 1) cst(ep + q * 2, e);
   }
   __syncthreads();
   cplx den = cmk(0.0, 0.0);
@@ -293,7 +301,7 @@ k_combine(int nw, int P, int G, double sqrt_tau, double xbar_cap, double ecap_ha
   if (eloc != nullptr) {
     cplx num = cmk(0.0, 0.0);
     for (int p = 0; p < P; ++p)
-      num = cfma(num, cmk(s_S[p][0], s_S[p][1]), cld(ep + ((size_t)w * P + p) * 2));
+      num = cfma(num, cmk(s_S[p][0], s_S[p][1]), cmk(s_E[p][0], s_E[p][1]));
     cplx el = good ? cdiv(num, den) : cmk(0.0, 0.0);
     if (!(__builtin_isfinite(el.re) && __builtin_isfinite(el.im))) bits |= AFQMC_NUMERIC_ELOC;
     else if (ecap_half > 0.0) el.re = fmin(fmax(el.re, ecap_lo), ecap_hi);
@@ -314,6 +322,16 @@ hipError_t launch_mt(const afqmc_ctx_s* c, int nw, const double* phiT, const dou
 
 }  // namespace
 
+// One wavefront per path shares an L slab between four paths through LDS and holds 1024
+// paths on the chip; k_contract_q needs no multiple of that and multiplies N rounded up to
+// 4 instead of 16.  M = 64, 256 vectors: N = 16, 1024 paths 1.18 ms here, 1.25 there; 2048
+// 2.32, 2.39; 1200 2.28, 1.50; 256 1.13, 0.36; M = 45, N = 11, 1332 paths 1.16, 0.63.
+bool contract_in_registers(const afqmc_ctx_s* c, int nw) {
+  if (!c->small || c->precision != AFQMC_PREC_FP64 || c->N <= 12) return false;
+  const long n = (long)nw * c->P, rounds = (n + 1023) / 1024;
+  return 100 * n >= 93 * 1024 * rounds;
+}
+
 hipError_t launch_contract(const afqmc_ctx_s* c, int nw, const double* phiT, const double* theta,
                            const double* logov, double* vb, double* ep) {
   if (nw <= 0) return hipSuccess;
@@ -326,12 +344,13 @@ hipError_t launch_contract(const afqmc_ctx_s* c, int nw, const double* phiT, con
   }
 }
 
-hipError_t launch_combine(const afqmc_ctx_s* c, int nw, const double* vb, const double* ep,
-                          const double* logov, double* xbar, double* eloc, int* flags) {
+hipError_t launch_combine(const afqmc_ctx_s* c, int nw, const double* vb, const double* epart,
+                          int nsplit, double* ep, const double* logov, double* xbar, double* eloc,
+                          int* flags) {
   if (nw <= 0) return hipSuccess;
   if (c->P > 64) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_combine, dim3(nw), dim3(64), 0, c->stream, nw, c->P, c->G, sqrt(c->dtau),
                      c->xbar_cap, c->ecap_half, c->ecap_center - c->ecap_half,
-                     c->ecap_center + c->ecap_half, vb, ep, logov, xbar, eloc, flags);
+                     c->ecap_center + c->ecap_half, vb, epart, nsplit, ep, logov, xbar, eloc, flags);
   return hipGetLastError();
 }
