@@ -192,6 +192,12 @@ hipError_t launch_taylor_g(const afqmc_ctx_s* c, int nw, const double* vmat, dou
 hipError_t launch_taylor_g_gen(const afqmc_ctx_s* c, int n, int spins, int n_taylor,
                                const double* vmat, const double* El, const double* Er,
                                const double* src, int src_ws, double* dst);
+// the same in FP64 with the blocks of a V side by side (k_taylor_q.hip), where that is
+// the faster form
+bool taylor_q_better(const afqmc_ctx_s* c, int n, int spins);
+hipError_t launch_taylor_q(const afqmc_ctx_s* c, int n, int spins, int n_taylor,
+                           const double* vmat, const double* El, const double* Er,
+                           const double* src, int src_ws, double* dst);
 // vmat[w] = i sqrt_s sum_k (y[w * xs + k] - xbar[w * xbs + k]) Lgen_k  (k < G;
 // xbar complex, may be null)
 // scratch (may be null): device memory free for the call (split coefficients of

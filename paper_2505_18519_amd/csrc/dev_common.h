@@ -4,7 +4,25 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+#include <utility>
+
 #define AFQMC_WAVE 64
+
+// After loads meant for a later use (the next trip of a loop): without it the compiler moves
+// them to that use (folding a loop-carried value into one load at the top of the trip),
+// and waits there.
+#define AFQMC_KEEP_AHEAD() asm volatile("" ::: "memory")
+
+// fn(0), ..., fn(n - 1) with compile-time indices (arrays they index stay in registers)
+template <class F, int... I>
+__device__ __forceinline__ void unroll_impl(F fn, std::integer_sequence<int, I...>) {
+  (fn(std::integral_constant<int, I>{}), ...);
+}
+template <int n, class F>
+__device__ __forceinline__ void unrolled(F fn) {
+  unroll_impl(fn, std::make_integer_sequence<int, n>{});
+}
 
 // ---------------------------------------------------------------------------
 // complex double, interleaved (re, im) in memory

@@ -32,29 +32,12 @@
 #include "afqmc_internal.h"
 #include "dev_common.h"
 
-#include <type_traits>
-#include <utility>
-
 namespace {
 
 // D(4x4, four blocks b) += A_b(4x4) B_b(4x4).  Lane l = 16 g + 4 b + i supplies
 // A_b[i][g] and B_b[g][i] and holds D_b[g][i].
 __device__ __forceinline__ double mfma_f64_4(double a, double b, double acc) {
   return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, acc, 0, 0, 0);
-}
-
-// After loads meant for the next trip of a loop: without it the compiler folds the
-// loop-carried value into one load at the top of the trip that uses it, and waits there.
-#define AFQMC_KEEP_AHEAD() asm volatile("" ::: "memory")
-
-// fn(0), ..., fn(n - 1) with compile-time indices (arrays they index stay in registers)
-template <class F, int... I>
-__device__ __forceinline__ void unroll_impl(F fn, std::integer_sequence<int, I...>) {
-  (fn(std::integral_constant<int, I>{}), ...);
-}
-template <int n, class F>
-__device__ __forceinline__ void unrolled(F fn) {
-  unroll_impl(fn, std::make_integer_sequence<int, n>{});
 }
 
 constexpr int GV = 4;  // vectors of a group

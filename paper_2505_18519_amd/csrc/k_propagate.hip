@@ -1075,6 +1075,8 @@ hipError_t taylor_g_dispatch(const afqmc_ctx_s* c, int n, int spins, int n_taylo
 hipError_t launch_taylor_g_gen(const afqmc_ctx_s* c, int n, int spins, int n_taylor,
                                const double* vmat, const double* El, const double* Er,
                                const double* src, int src_ws, double* dst) {
+  if (taylor_q_better(c, n, spins))
+    return launch_taylor_q(c, n, spins, n_taylor, vmat, El, Er, src, src_ws, dst);
   return taylor_g_dispatch<double>(c, n, spins, n_taylor, vmat, El, Er, src, src_ws, dst);
 }
 
@@ -1103,7 +1105,7 @@ hipError_t launch_taylor_g(const afqmc_ctx_s* c, int nw, const double* vmat, dou
   }
   if (prop_f32(c))
     return taylor_g_dispatch<float>(c, nw, 2, c->n_taylor, vmat, c->d_Eh, c->d_Eh, phi, 2, phi);
-  return taylor_g_dispatch<double>(c, nw, 2, c->n_taylor, vmat, c->d_Eh, c->d_Eh, phi, 2, phi);
+  return launch_taylor_g_gen(c, nw, 2, c->n_taylor, vmat, c->d_Eh, c->d_Eh, phi, 2, phi);
 }
 
 // V split for the split-BF16 propagation of BF16 contexts: Vs [nw][Re hi, Re lo,
