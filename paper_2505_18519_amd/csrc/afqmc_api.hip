@@ -624,7 +624,11 @@ static hipError_t contraction_kernels(afqmc_ctx c, int32_t nw, const double* phi
   hipError_t e;
   const double* epart = ep;
   int nsplit = 1;
-  if (c->precision != AFQMC_PREC_FP64 && !c->ctrial) {
+  if (c->precision == AFQMC_PREC_FP32 && !c->ctrial) {
+    nsplit = contract_f32_splits(c, nw);
+    if (nsplit > 1) epart = part;
+    e = launch_contract_f32(c, nw, nsplit, phiT, th, lo, vb, nsplit > 1 ? part : ep);
+  } else if (c->precision != AFQMC_PREC_FP64 && !c->ctrial) {
     e = launch_contract_sh(c, nw, phiT, th, lo, vb, ep);
   } else if (c->precision != AFQMC_PREC_FP64) {
     e = launch_contract_g(c, nw, phiT, th, lo, vb, ep);

@@ -233,7 +233,12 @@ hipError_t launch_trial_slices(const afqmc_ctx_s* c, int n, const double* y, dou
                                double* vbuf);
 hipError_t launch_qr_g(const afqmc_ctx_s* c, int nw, double* phi, double* logov, double* shift);
 hipError_t launch_to_float(const afqmc_ctx_s* c, size_t n, const double* src, float* dst);
-// FP32 (real trial), split-BF16 and BF16 contractions, two paths per workgroup
+// FP32 contraction (real trial), over ranges of the vectors as contract_q_splits
+int contract_f32_splits(const afqmc_ctx_s* c, int nw);
+hipError_t launch_contract_f32(const afqmc_ctx_s* c, int nw, int nsplit, const double* phiT,
+                               const double* theta, const double* logov, double* vb,
+                               double* epart);
+// split-BF16 and BF16 contractions
 hipError_t launch_contract_sh(const afqmc_ctx_s* c, int nw, const double* phiT,
                               const double* theta, const double* logov, double* vb, double* ep);
 hipError_t launch_to_bf16(const afqmc_ctx_s* c, size_t n, const double* src, unsigned short* hi,

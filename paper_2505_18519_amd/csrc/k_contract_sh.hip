@@ -1,15 +1,12 @@
-// Cholesky-vector contraction with reduced-precision matrix-core products and
-// FP32 accumulation: FP32, split BF16 and BF16 (AFQMC_PREC_FP32 with a real
-// trial, AFQMC_PREC_BF16X3, AFQMC_PREC_BF16).  Same quantities as k_contract
-// (Sec. III.A, Eq. local-obs; Eq. shift1):
+// Cholesky-vector contraction with BF16 matrix-core products and FP32
+// accumulation: split BF16 and BF16 (AFQMC_PREC_BF16X3, AFQMC_PREC_BF16).  Same
+// quantities as k_contract (Sec. III.A, Eq. local-obs; Eq. shift1):
 //   Y_g = Phi_T^T L_g,  f_g^s = Y_g Theta^s,  vb_g = sum_s tr f_g^s,
 //   E_p = sum_s tr(Phi_T^T h1' Theta^s) + 1/2 sum_g [vb_g^2 - sum_s tr(f_g^s f_g^s)].
 //
 // Products: lane (g, c) supplies KV consecutive k values of one row of A and
-// one column of B and holds D[4g + r][c].  BF16 (and split BF16): one
-// v_mfma_f32_16x16x32_bf16 per 32-wide k block, KV = 8 (k = 32 u + 8 g + j);
-// FP32: four v_mfma_f32_16x16x4f32 per 16-wide k block, KV = 4 (k = 16 u +
-// 4 g + j, the j-th product on the j-th value).  A and B take the same lane
+// one column of B and holds D[4g + r][c]: one v_mfma_f32_16x16x32_bf16 per
+// 32-wide k block, KV = 8 (k = 32 u + 8 g + j).  A and B take the same lane
 // layout of k, so the product is the contraction over k whatever order the
 // matrix core visits the block in.
 // Split BF16: every operand x is carried as x_hi = bf16(x) and
@@ -29,7 +26,7 @@
 // row tile, its A operands read from the shared slab.  Y_g^T is rounded to the
 // operand form once, as stage 1 leaves it, and stored in LDS in the accumulator
 // layout, which is stage 2's A-operand layout (rows 4g .. 4g+3 of a column in
-// one lane; in BF16 the two 4-row groups of one operand side by side, so that
+// one lane, the two 4-row groups of one operand side by side, so that
 // an operand is one 16-byte read); f is transposed through LDS for tr(f f), as
 // separate real and imaginary planes whose rows start on 16-byte boundaries.
 // Each lane's eight products of FP32 entries of f for tr(f f) are summed in
@@ -75,20 +72,19 @@ __device__ __forceinline__ fx4 fx4_zero() {
 
 // Operand forms of the contraction.  An operand is what one lane supplies to
 // one k block: KV consecutive k values of one row or column, as NP parts of
-// type V (FP32: float4; BF16: eight BF16 values).  The Y^T tile is kept in
+// type V (eight BF16 values).  The Y^T tile is kept in
 // LDS in 4-row groups of type V4 (the accumulator layout of stage 1), two of
 // which make one BF16 operand.
-enum { FM_BF16 = 0, FM_BF16X3 = 1, FM_FP32 = 2 };
+enum { FM_BF16 = 0, FM_BF16X3 = 1 };
 template <int FM>
 struct Form {
   static constexpr bool X3 = FM == FM_BF16X3;
-  static constexpr bool F32 = FM == FM_FP32;
   static constexpr int NP = X3 ? 2 : 1;             // parts: hi (and lo)
   static constexpr int NB = FM == FM_BF16 ? 2 : 1;  // slab buffers (shared slabs)
-  static constexpr int KV = F32 ? 4 : 8;            // k values per lane and block
+  static constexpr int KV = 8;                      // k values per lane and block
   static constexpr int KB = 4 * KV;                 // k per block
-  typedef typename std::conditional<F32, fx4, sx8>::type V;
-  typedef typename std::conditional<F32, fx4, sx4>::type V4;
+  typedef sx8 V;
+  typedef sx4 V4;
   struct Op {
     V p[NP];
   };
@@ -98,50 +94,36 @@ struct Form {
   // hi (and lo) parts of four values
   __device__ __forceinline__ static Op4 make4(float a, float b, float c, float d) {
     Op4 o;
-    if constexpr (F32) {
-      o.p[0] = fx4{a, b, c, d};
-    } else {
-      const unsigned h01 = pk_bf16(a, b), h23 = pk_bf16(c, d);
-      o.p[0] = __builtin_bit_cast(sx4, (unsigned long long)h01 | ((unsigned long long)h23 << 32));
-      if constexpr (X3) {
-        const unsigned l01 = pk_bf16(a - bf_lo(h01), b - bf_hi(h01));
-        const unsigned l23 = pk_bf16(c - bf_lo(h23), d - bf_hi(h23));
-        o.p[NP - 1] =
-            __builtin_bit_cast(sx4, (unsigned long long)l01 | ((unsigned long long)l23 << 32));
-      }
+    const unsigned h01 = pk_bf16(a, b), h23 = pk_bf16(c, d);
+    o.p[0] = __builtin_bit_cast(sx4, (unsigned long long)h01 | ((unsigned long long)h23 << 32));
+    if constexpr (X3) {
+      const unsigned l01 = pk_bf16(a - bf_lo(h01), b - bf_hi(h01));
+      const unsigned l23 = pk_bf16(c - bf_lo(h23), d - bf_hi(h23));
+      o.p[NP - 1] =
+          __builtin_bit_cast(sx4, (unsigned long long)l01 | ((unsigned long long)l23 << 32));
     }
     return o;
   }
   __device__ __forceinline__ static Op make(const float (&x)[KV]) {
     Op o;
-    if constexpr (F32) {
-      o.p[0] = fx4{x[0], x[1], x[2], x[3]};
-    } else {
-      const Op4 a = make4(x[0], x[1], x[2], x[3]), b = make4(x[4], x[5], x[6], x[7]);
+    const Op4 a = make4(x[0], x[1], x[2], x[3]), b = make4(x[4], x[5], x[6], x[7]);
 #pragma unroll
-      for (int part = 0; part < NP; ++part) o.p[part] = join(a.p[part], b.p[part]);
-    }
+    for (int part = 0; part < NP; ++part) o.p[part] = join(a.p[part], b.p[part]);
     return o;
   }
   __device__ __forceinline__ static sx8 join(sx4 a, sx4 b) {
     return sx8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
   }
   __device__ __forceinline__ static fx4 mma(const Op& a, const Op& b, fx4 acc) {
-    if constexpr (F32) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.p[0][j], b.p[0][j], acc, 0, 0, 0);
-    } else {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bfx8, a.p[0]),
+                                                  __builtin_bit_cast(bfx8, b.p[0]), acc, 0, 0, 0);
+    if constexpr (X3) {
       acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bfx8, a.p[0]),
-                                                    __builtin_bit_cast(bfx8, b.p[0]), acc, 0, 0, 0);
-      if constexpr (X3) {
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bfx8, a.p[0]),
-                                                      __builtin_bit_cast(bfx8, b.p[NP - 1]), acc, 0,
-                                                      0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bfx8, a.p[NP - 1]),
-                                                      __builtin_bit_cast(bfx8, b.p[0]), acc, 0, 0,
-                                                      0);
-      }
+                                                    __builtin_bit_cast(bfx8, b.p[NP - 1]), acc, 0,
+                                                    0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bfx8, a.p[NP - 1]),
+                                                    __builtin_bit_cast(bfx8, b.p[0]), acc, 0, 0,
+                                                    0);
     }
     return acc;
   }
@@ -199,10 +181,9 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
   constexpr int NCH = (NU + 63) / 64;          // 1 KB chunks per slab (the last may be partial)
   constexpr int YT = (MTP / 4) * NT;           // 4-row groups (V4) of one Y^T tile part
   // Slabs in LDS when several paths share them: plain BF16 double-buffered (the
-  // next slab loads during the whole vector), split BF16 (hi and lo) and FP32
-  // (twice the bytes) single, the next slab loading from the barrier after
-  // stage 1 on.  One path per workgroup (DIRECT): no slab in LDS; each
-  // wavefront loads its stage-1 A operands of vector g + 1 from global memory
+  // next slab loads during the whole vector), split BF16 (hi and lo) single,
+  // the next slab loading from the barrier after stage 1 on.  One path per
+  // workgroup (DIRECT): no slab in LDS; each wavefront loads its stage-1 A operands of vector g + 1 from global memory
   // into registers during vector g.  The Y^T tile is single: it is rewritten
   // only after the barrier that follows every stage-2 read of it.
   constexpr bool DIRECT = BCP == 1;
@@ -230,14 +211,9 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
   const int sc = valid ? s : n_samples - 1;
   const bool active = valid && !__builtin_isinf(logov[2 * sc]);
 
-  // Y^T tile index of 4-row group grp, column col: BF16 keeps groups 2p and 2p + 1 of a
-  // column side by side (one stage-2 operand is one 16-byte read)
-  auto yidx = [&](int grp, int col) {
-    if constexpr (Fm::F32)
-      return grp * NT + col;
-    else
-      return ((grp >> 1) * NT + col) * 2 + (grp & 1);
-  };
+  // Y^T tile index of 4-row group grp, column col: groups 2p and 2p + 1 of a column side
+  // by side (one stage-2 operand is one 16-byte read)
+  auto yidx = [&](int grp, int col) { return ((grp >> 1) * NT + col) * 2 + (grp & 1); };
   auto copy_slab = [&](int slab, int buf) {
 #pragma unroll
     for (int part = 0; part < NP; ++part) {
@@ -346,7 +322,7 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
     for (int q = 0; q < S1MAX; ++q) {
       const int tp = wv + NWV * q;
       if (tp < KT) {
-        if constexpr (!Fm::F32 && NTC == 2) {
+        if constexpr (NTC == 2) {
           // lanes of rows g and g ^ 1 (16 apart) trade tiles: row 2h keeps tile 0 and takes
           // its row 2h + 1 partner's tile 0 (the next 4-row group of the same column); row
           // 2h + 1 takes row 2h's tile 1; each lane then stores one whole BF16 operand, the
@@ -378,7 +354,7 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
     // single buffers: every stage-1 read of this slab is done, the next one can load
     if (NB == 1 && gam < G) copy_slab(gam + 1, 0);
     // stage 2: packed f[it][wv], A[c][KV g + j] = Y^T[KB t + KV g + j][16it + c]: the
-    // 4-row group (KB t + KV g) / 4, and for BF16 the next one too
+    // 4-row group (KB t + KV g) / 4 and the next one
     fx4 f[NTC][2];
 #pragma unroll
     for (int it = 0; it < NTC; ++it) f[it][0] = f[it][1] = fx4_zero();
@@ -391,10 +367,7 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
 #pragma unroll
         for (int part = 0; part < NP; ++part) {
           const V4* yg = Yb + part * YT + yidx(grp, 16 * it + c);
-          if constexpr (Fm::F32)
-            a.p[part] = yg[0];
-          else
-            a.p[part] = *reinterpret_cast<const V*>(yg);  // groups grp, grp + 1: one 16-byte read
+          a.p[part] = *reinterpret_cast<const V*>(yg);  // groups grp, grp + 1: one 16-byte read
         }
         f[it][0] = Fm::mma(a, th[0][t], f[it][0]);
         f[it][1] = Fm::mma(a, th[1][t], f[it][1]);
@@ -545,15 +518,14 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
     for (int q = lane; q < 2 * G; q += 64) vb[(size_t)s * G * 2 + q] = 0.0;
 }
 
-// slabs: buffers x parts x bytes per entry = 2 x 1 x 2 (BF16 shared; 1 x 1 x 2
-// for one path), 1 x 2 x 2 (split BF16) or 1 x 1 x 4 (FP32), over MT x MTP
-// entries (MTP: k padded to whole blocks); Y^T tiles: parts x bytes per 4-row
-// group = 1 x 8 (BF16), 2 x 8 (split BF16), 1 x 16 (FP32)
+// slabs: buffers x parts x bytes per entry = 2 x 1 x 2 (BF16 shared; none for one
+// path) or 1 x 2 x 2 (split BF16), over MT x MTP entries (MTP: k padded to whole
+// blocks); Y^T tiles: parts x bytes per 4-row group = 1 x 8 (BF16), 2 x 8 (split BF16)
 size_t lds_bytes_s(int KT, int NTC, int NCP, int FM, int BCP) {
   const int MT = 16 * KT, NT = 16 * NTC, NWV = NCP;
-  const int KB = FM == FM_FP32 ? 16 : 32, MTP = (MT + KB - 1) / KB * KB;
+  const int KB = 32, MTP = (MT + KB - 1) / KB * KB;
   size_t b = BCP == 1 ? 0 : (size_t)4 * MT * MTP;  // slabs (none with one path per workgroup)
-  b += (size_t)BCP * (MTP / 4) * NT * (FM == FM_FP32 ? 16 : FM == FM_BF16X3 ? 16 : 8);  // Y^T tiles
+  b += (size_t)BCP * (MTP / 4) * NT * (FM == FM_BF16X3 ? 16 : 8);  // Y^T tiles
   b += (size_t)BCP * NT * (16 * NCP + 4) * 2 * 4;     // packed f (FP32)
   b += (size_t)BCP * BFL * NWV * 16 * 2 * 4;          // staged diagonals (FP32)
   b += (size_t)BCP * NWV * 2 * 8 + (size_t)BCP * NWV * 4 * 8;
@@ -614,18 +586,6 @@ __global__ void k_to_bf16_op(size_t n, int MT, const double* __restrict__ src,
   if (lo != nullptr) lo[o] = f2bf(x - bf2f(h));
 }
 
-// the same order in FP32
-__global__ void k_to_f32_op(size_t n, int MT, const double* __restrict__ src,
-                            float* __restrict__ dst) {
-  const size_t o = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (o >= n) return;
-  const int KT = MT / 16;
-  const size_t slab = o / ((size_t)MT * MT);
-  const int r = (int)(o % ((size_t)MT * MT));
-  const int j = r & 3, cc = (r >> 2) & 15, gg = (r >> 6) & 3, t = (r >> 8) % KT, tp = (r >> 8) / KT;
-  dst[o] = (float)src[slab * MT * MT + (size_t)(16 * tp + cc) * MT + 16 * t + 4 * gg + j];
-}
-
 }  // namespace
 
 hipError_t launch_contract_sh(const afqmc_ctx_s* c, int nw, const double* phiT,
@@ -633,9 +593,6 @@ hipError_t launch_contract_sh(const afqmc_ctx_s* c, int nw, const double* phiT,
   if (nw <= 0) return hipSuccess;
   if (c->ctrial) return hipErrorInvalidValue;  // real trial determinants only
   switch (c->precision) {
-    case AFQMC_PREC_FP32:
-      if (c->d_Lpad32 == nullptr) return hipErrorInvalidValue;
-      return dispatch_s<FM_FP32>(c, nw, c->d_Lpad32, nullptr, phiT, theta, logov, vb, ep);
     case AFQMC_PREC_BF16X3:
       if (c->d_Lbf == nullptr || c->d_Lbf_lo == nullptr) return hipErrorInvalidValue;
       return dispatch_s<FM_BF16X3>(c, nw, c->d_Lbf, c->d_Lbf_lo, phiT, theta, logov, vb, ep);
@@ -653,12 +610,5 @@ hipError_t launch_to_bf16(const afqmc_ctx_s* c, size_t n, const double* src, uns
   // the shared-slab kernels' A-operand order (lo only for the split form)
   hipLaunchKernelGGL(k_to_bf16_op, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, n,
                      c->MT, src, hi, lo);
-  return hipGetLastError();
-}
-
-hipError_t launch_to_f32_op(const afqmc_ctx_s* c, size_t n, const double* src, float* dst) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_to_f32_op, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, n,
-                     c->MT, src, dst);
   return hipGetLastError();
 }
