@@ -629,7 +629,9 @@ static hipError_t contraction_kernels(afqmc_ctx c, int32_t nw, const double* phi
     if (nsplit > 1) epart = part;
     e = launch_contract_f32(c, nw, nsplit, phiT, th, lo, vb, nsplit > 1 ? part : ep);
   } else if (c->precision != AFQMC_PREC_FP64 && !c->ctrial) {
-    e = launch_contract_sh(c, nw, phiT, th, lo, vb, ep);
+    nsplit = contract_sh_splits(c, nw);
+    if (nsplit > 1) epart = part;
+    e = launch_contract_sh(c, nw, nsplit, phiT, th, lo, vb, nsplit > 1 ? part : ep);
   } else if (c->precision != AFQMC_PREC_FP64) {
     e = launch_contract_g(c, nw, phiT, th, lo, vb, ep);
   } else if (contract_in_registers(c, nw)) {

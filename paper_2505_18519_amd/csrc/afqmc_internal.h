@@ -238,9 +238,11 @@ int contract_f32_splits(const afqmc_ctx_s* c, int nw);
 hipError_t launch_contract_f32(const afqmc_ctx_s* c, int nw, int nsplit, const double* phiT,
                                const double* theta, const double* logov, double* vb,
                                double* epart);
-// split-BF16 and BF16 contractions
-hipError_t launch_contract_sh(const afqmc_ctx_s* c, int nw, const double* phiT,
-                              const double* theta, const double* logov, double* vb, double* ep);
+// split-BF16 and BF16 contractions, likewise
+int contract_sh_splits(const afqmc_ctx_s* c, int nw);
+hipError_t launch_contract_sh(const afqmc_ctx_s* c, int nw, int nsplit, const double* phiT,
+                              const double* theta, const double* logov, double* vb,
+                              double* epart);
 hipError_t launch_to_bf16(const afqmc_ctx_s* c, size_t n, const double* src, unsigned short* hi,
                           unsigned short* lo);
 hipError_t launch_to_f32_op(const afqmc_ctx_s* c, size_t n, const double* src, float* dst);

@@ -157,12 +157,14 @@ typedef __attribute__((address_space(1))) void* gbl_ptr_t;
 
 // FULL: N = 16 NTC (every column tile full, NCP = 2 NTC), so the packed
 // columns are the two spins' tiles in order and no column or row is padding.
-template <int KT, int NTC, int NCP, int FM, bool FULL, int BCP>
+// RANGES: gridDim.y workgroups share a path's vectors (a compile-time choice: with the
+// range in registers the full-chip calls below took 1 to 5 % longer).
+template <int KT, int NTC, int NCP, int FM, bool FULL, int BCP, bool RANGES>
 __global__ void __launch_bounds__(64 * NCP * BCP) __attribute__((amdgpu_waves_per_eu(2)))
 k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
                const void* __restrict__ Lop_lo, const double* __restrict__ phiT,
                const double* __restrict__ theta,
-               const double* __restrict__ logov, double* __restrict__ vb, double* __restrict__ ep) {
+               const double* __restrict__ logov, double* __restrict__ vb, double* __restrict__ epart) {
   constexpr int MT = 16 * KT;
   constexpr int NWV = NCP;                     // wavefronts per path
   constexpr int PW = 16 * NCP + 4;             // row length of the staged f (packed columns; 16-byte rows)
@@ -210,6 +212,15 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
   const bool valid = s < n_samples;            // every wavefront takes part in the barriers
   const int sc = valid ? s : n_samples - 1;
   const bool active = valid && !__builtin_isinf(logov[2 * sc]);
+  // this workgroup's range of the vectors, in whole blocks of BFL (so the first has an even
+  // number); the last range has h1' (slab G) too
+  const int nblk = (G + BFL - 1) / BFL;
+  const int gbeg =
+      RANGES ? __builtin_amdgcn_readfirstlane((int)blockIdx.y * nblk / (int)gridDim.y * BFL) : 0;
+  const int gnext = RANGES ? __builtin_amdgcn_readfirstlane(((int)blockIdx.y + 1) * nblk /
+                                                            (int)gridDim.y * BFL)
+                           : G;
+  const int gend = !RANGES || gnext >= G ? G : gnext - 1;
 
   // Y^T tile index of 4-row group grp, column col: groups 2p and 2p + 1 of a column side
   // by side (one stage-2 operand is one 16-byte read)
@@ -243,9 +254,9 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
     }
   };
   if constexpr (DIRECT)
-    load_ops(0);
+    load_ops(gbeg);
   else
-    copy_slab(0, 0);
+    copy_slab(gbeg, 0);
   if (MTP > MT) {  // the Y^T rows of a padded k block are never written: zero them once
     for (int q = threadIdx.x; q < BCP * NP * ((MTP - MT) / 4) * NT; q += blockDim.x) {
       const int per = ((MTP - MT) / 4) * NT;
@@ -283,14 +294,14 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
 #pragma unroll
     for (int ri = 0; ri < 2; ++ri) th[ri][t] = Fm::make(w[ri]);
   }
-  if constexpr (!DIRECT) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's chunks of slab 0 are in LDS
+  if constexpr (!DIRECT) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's chunks of the first slab are in LDS
   __syncthreads();
 
   V4* Yb = sY + pw * NP * YT;  // the path's Y^T tile
   float* Fp = sF + (size_t)pw * 2 * NT * PW;
   float* Dp = sD + (size_t)pw * BFL * 2 * NWV * 16;
   double ex_re = 0.0, ex_im = 0.0, vb2_re = 0.0, vb2_im = 0.0, e1_re = 0.0, e1_im = 0.0;
-  for (int gam = 0; gam <= G; ++gam) {
+  for (int gam = gbeg; gam <= gend; ++gam) {
     const int b = NB == 2 ? (gam & 1) : 0;
     // stage 1: Y^T tiles (tp, ct) from the shared slab
     fx4 y1[S1MAX][NTC];
@@ -315,9 +326,9 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
           for (int ct = 0; ct < NTC; ++ct) y1[q][ct] = Fm::mma(a, bT[ct][t], y1[q][ct]);
         }
     }
-    if (DIRECT && gam < G) load_ops(gam + 1);
+    if (DIRECT && gam < gend) load_ops(gam + 1);
     // buffer b ^ 1 was last read in stage 1 of the previous vector, before its barriers
-    if (NB == 2 && gam < G) copy_slab(gam + 1, b ^ 1);
+    if (NB == 2 && gam < gend) copy_slab(gam + 1, b ^ 1);
 #pragma unroll
     for (int q = 0; q < S1MAX; ++q) {
       const int tp = wv + NWV * q;
@@ -352,7 +363,7 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
     }
     __syncthreads();
     // single buffers: every stage-1 read of this slab is done, the next one can load
-    if (NB == 1 && gam < G) copy_slab(gam + 1, 0);
+    if (NB == 1 && gam < gend) copy_slab(gam + 1, 0);
     // stage 2: packed f[it][wv], A[c][KV g + j] = Y^T[KB t + KV g + j][16it + c]: the
     // 4-row group (KB t + KV g) / 4 and the next one
     fx4 f[NTC][2];
@@ -510,12 +521,12 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
       xi += sT[(pw * NWV + w) * 4 + 1];
     }
     const double br = sT[pw * NWV * 4 + 2], bi = sT[pw * NWV * 4 + 3];
-    double* o = ep + (size_t)s * 2;
+    double* o = epart + ((RANGES ? (size_t)blockIdx.y * n_samples : 0) + s) * 2;
     o[0] = active ? e1_re + 0.5 * br - 0.5 * xr : 0.0;
     o[1] = active ? e1_im + 0.5 * bi - 0.5 * xi : 0.0;
   }
   if (valid && !active && wv == 0)
-    for (int q = lane; q < 2 * G; q += 64) vb[(size_t)s * G * 2 + q] = 0.0;
+    for (int q = 2 * gbeg + lane; q < 2 * min(gend + 1, G); q += 64) vb[(size_t)s * G * 2 + q] = 0.0;
 }
 
 // slabs: buffers x parts x bytes per entry = 2 x 1 x 2 (BF16 shared; none for one
@@ -533,29 +544,30 @@ size_t lds_bytes_s(int KT, int NTC, int NCP, int FM, int BCP) {
 }
 
 template <int KT, int NTC, int NCP, int FM, bool FULL, int BCP>
-hipError_t launch_sh(const afqmc_ctx_s* c, int nw, const void* L, const void* L_lo,
+hipError_t launch_sh(const afqmc_ctx_s* c, int nw, int nsplit, const void* L, const void* L_lo,
                       const double* phiT, const double* theta, const double* logov, double* vb,
-                      double* ep) {
+                      double* epart) {
   const int n = nw * c->P;
   const size_t lds = lds_bytes_s(KT, NTC, NCP, FM, BCP);
-  auto kern = k_contract_sh<KT, NTC, NCP, FM, FULL, BCP>;
+  auto kern = nsplit > 1 ? k_contract_sh<KT, NTC, NCP, FM, FULL, BCP, true>
+                         : k_contract_sh<KT, NTC, NCP, FM, FULL, BCP, false>;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((n + BCP - 1) / BCP), dim3(64 * NCP * BCP), lds, c->stream, n,
-                     c->M, c->N, c->G, L, L_lo, phiT, theta, logov, vb, ep);
+  hipLaunchKernelGGL(kern, dim3((n + BCP - 1) / BCP, nsplit), dim3(64 * NCP * BCP), lds,
+                     c->stream, n, c->M, c->N, c->G, L, L_lo, phiT, theta, logov, vb, epart);
   return hipGetLastError();
 }
 
 template <int FM>
-hipError_t dispatch_s(const afqmc_ctx_s* c, int nw, const void* L, const void* L_lo,
+hipError_t dispatch_s(const afqmc_ctx_s* c, int nw, int nsplit, const void* L, const void* L_lo,
                       const double* phiT, const double* theta, const double* logov, double* vb,
-                      double* ep) {
+                      double* epart) {
   const int KT = c->MT / 16, NTC = (c->N + 15) / 16, NCP = (2 * c->N + 15) / 16;
   const bool full = c->N == 16 * NTC;
 #define AFQMC_BS(KK, NC, NP, FL)                           \
   if (KT == KK && NTC == NC && NCP == NP && full == FL) \
-    return launch_sh<KK, NC, NP, FM, FL, bcp_for(FM, NP)>(c, nw, L, L_lo, phiT, theta, logov, vb, ep);
+    return launch_sh<KK, NC, NP, FM, FL, bcp_for(FM, NP)>(c, nw, nsplit, L, L_lo, phiT, theta, logov, vb, epart);
 #define AFQMC_BS1(KK) AFQMC_BS(KK, 1, 1, false) AFQMC_BS(KK, 1, 2, false) AFQMC_BS(KK, 1, 2, true)
 #define AFQMC_BS2(KK) AFQMC_BS(KK, 2, 3, false) AFQMC_BS(KK, 2, 4, false) AFQMC_BS(KK, 2, 4, true)
   AFQMC_BS1(1) AFQMC_BS1(2) AFQMC_BS1(3) AFQMC_BS1(4)
@@ -588,17 +600,43 @@ __global__ void k_to_bf16_op(size_t n, int MT, const double* __restrict__ src,
 
 }  // namespace
 
-hipError_t launch_contract_sh(const afqmc_ctx_s* c, int nw, const double* phiT,
-                              const double* theta, const double* logov, double* vb, double* ep) {
+// Ranges of g, for calls that do not fill one round of the chip (eight wavefronts a CU): the
+// fewest that fill the rounds to within 4 %, at least two blocks of BFL vectors to a range.
+// 40 paths of M = 96, N = 24, 384 vectors: BF16 0.80 -> 0.083 ms, split BF16 1.64 -> 0.155;
+// 200 paths of M = 80, N = 26: 0.30 -> 0.18 and 0.79 -> 0.37.  Past one round a split gained
+// little (2 % at 1.2 rounds) or lost (9 % at 5.5 rounds).  k P <= M^2 keeps the partial sums
+// within the workspace's V buffer, which holds them.
+int contract_sh_splits(const afqmc_ctx_s* c, int nw) {
+  const int ncp = (2 * c->N + 15) / 16;
+  const int bcp = bcp_for(c->precision == AFQMC_PREC_BF16 ? FM_BF16 : FM_BF16X3, ncp);
+  const long units = ((long)nw * c->P + bcp - 1) / bcp;
+  const long slots = 256 * (ncp * bcp < 8 ? 8 / (ncp * bcp) : 1);
+  const int nblk = (c->G + BFL - 1) / BFL;
+  int best = 1;
+  double fill = 0.0;
+  if (units > slots) return 1;
+  for (int k = 1; k <= 16 && k * 2 <= nblk && k * c->P <= c->M * c->M; ++k) {
+    const long u = units * k;
+    const double x = (double)u / (double)((u + slots - 1) / slots * slots);
+    if (x > fill + 0.04) {
+      best = k;
+      fill = x;
+    }
+  }
+  return best;
+}
+
+hipError_t launch_contract_sh(const afqmc_ctx_s* c, int nw, int nsplit, const double* phiT,
+                              const double* theta, const double* logov, double* vb, double* epart) {
   if (nw <= 0) return hipSuccess;
   if (c->ctrial) return hipErrorInvalidValue;  // real trial determinants only
   switch (c->precision) {
     case AFQMC_PREC_BF16X3:
       if (c->d_Lbf == nullptr || c->d_Lbf_lo == nullptr) return hipErrorInvalidValue;
-      return dispatch_s<FM_BF16X3>(c, nw, c->d_Lbf, c->d_Lbf_lo, phiT, theta, logov, vb, ep);
+      return dispatch_s<FM_BF16X3>(c, nw, nsplit, c->d_Lbf, c->d_Lbf_lo, phiT, theta, logov, vb, epart);
     case AFQMC_PREC_BF16:
       if (c->d_Lbf == nullptr) return hipErrorInvalidValue;
-      return dispatch_s<FM_BF16>(c, nw, c->d_Lbf, nullptr, phiT, theta, logov, vb, ep);
+      return dispatch_s<FM_BF16>(c, nw, nsplit, c->d_Lbf, nullptr, phiT, theta, logov, vb, epart);
     default:
       return hipErrorInvalidValue;
   }
