@@ -19,14 +19,13 @@ namespace {
 // ---------------------------------------------------------------------------
 // V build: with c = xi - xbar, R = sum_g Re(c_g) L_g and Q = sum_g Im(c_g) L_g,
 // V = sqrt(tau) (-Q + i R).  A (walkers x G) by (G x M^2) product on the matrix
-// cores, tiled through LDS: a workgroup of four wavefronts takes VB_W = 64
-// walkers by VB_E matrix entries (64 in FP64, 128 in FP32) and walks G in
-// chunks of VB_KC vectors.  Each chunk's c (real and imaginary planes) and L
-// entries are read from global memory once per workgroup, converted to T,
-// and staged in double-buffered LDS while the previous chunk's products run;
-// wavefront (wh, eh) holds 2 walker tiles by VB_E / 32 entry tiles of R and Q
-// accumulators, so one staged c value feeds VB_E / 32 products and one L value
-// four.  Row w of xi starts at w * xs and of xbar at w * xbs; xbar may be null
+// cores, tiled through LDS: a workgroup of four wavefronts takes 32 WT walkers by
+// VB_E matrix entries (64 in FP64, 128 in FP32) and walks G in chunks of VB_KC
+// vectors.  Each chunk's xi, xbar and L entries are read from global memory once per
+// workgroup into registers while the previous chunk's products run, and after them
+// masked, converted to T and stored to the other of two LDS buffers; wavefront
+// (wh, eh) holds WT walker tiles by VB_E / 32 entry tiles of R and Q accumulators.
+// Row w of xi starts at w * xs and of xbar at w * xbs; xbar may be null
 // (c = xi): the trial slices use this with the generators A_k and their block
 // of y, the back-propagation with a walker's recorded fields.  XB = false (no
 // xbar): Q = 0 and only the R products run.  With T = float (mixed-precision
@@ -34,28 +33,37 @@ namespace {
 // on v_mfma_f32_16x16x4f32 with FP32 accumulation over g.  RO (real output,
 // with XB = false): the trial generators' U[s] = c sum_k y[s][k] A_k, stored
 // as one real FP64 entry per (row, entry), scaled by sqrt_tau = c.
-constexpr int VB_W = 64;   // walkers per workgroup
+//
+// Bound by the matrix cores (45 % busy) and, with few vectors, by the writes: M = 64,
+// 4096 rows, 64 generators 74 -> 56 us (30 us of products, 28 us of writes), where each
+// load was waited for on its own before a chunk's products; M = 72, 288 vectors, 700
+// walkers 149 -> 122 us, 58 us of products.
+constexpr int VB_W = 64;   // walkers per workgroup of the split-BF16 form
 constexpr int VB_KC = 16;  // vectors per staged chunk
 // LDS rows are padded by 16 values, so that the two k rows one 32-lane half of
 // a wavefront reads (g = 0, 1) fall on different banks
-template <typename T>
+template <typename T, int WT>
 struct VbShape {
+  static constexpr int W = 32 * WT;                   // walkers per workgroup
   static constexpr int ET = sizeof(T) == 4 ? 4 : 2;  // entry tiles per wavefront
   static constexpr int E = 32 * ET;                   // entries per workgroup
-  static constexpr int SAW = VB_W + 16, SBE = E + 16; // padded LDS rows of c and L
+  static constexpr int SAW = W + 16, SBE = E + 16;    // padded LDS rows of c and L
 };
-template <typename T, bool XB>
+template <typename T, int WT, bool XB>
 size_t vb_lds_bytes() {
-  typedef VbShape<T> S;
+  typedef VbShape<T, WT> S;
   return (size_t)2 * VB_KC * ((XB ? 2 : 1) * S::SAW + S::SBE) * sizeof(T);
 }
-template <typename T, bool XB, bool RO = false>
+// rows of xi and xbar may start at any multiple of 8 bytes
+typedef double dx2_a8 __attribute__((ext_vector_type(2), aligned(8)));
+template <typename T, int WT, bool XB, bool RO = false>
 __global__ void __launch_bounds__(256)
-k_vbuild(int nw, int G, int MM, int xs, int xbs, double sqrt_tau, const double* __restrict__ L,
-         const double* __restrict__ xi, const double* __restrict__ xbar, double* __restrict__ vmat) {
+k_vbuild(int nw, int G, int MM, int xs, int xbs, double sqrt_tau, const double* L,
+         const double* xi, const double* xbar, double* __restrict__ vmat) {
   typedef ::MM<T> mm;  // (the parameter MM is the number of matrix entries)
   typedef typename mm::acc_t acc_t;
-  constexpr int ET = VbShape<T>::ET, E = VbShape<T>::E, SAW = VbShape<T>::SAW, SBE = VbShape<T>::SBE;
+  typedef VbShape<T, WT> Sh;
+  constexpr int W = Sh::W, ET = Sh::ET, E = Sh::E, SAW = Sh::SAW, SBE = Sh::SBE;
   constexpr int NA = XB ? 2 : 1;                    // c planes (re, im)
   constexpr int CA = NA * VB_KC * SAW;              // staged c values per chunk
   constexpr int CH = CA + VB_KC * SBE;              // staged values per chunk
@@ -64,60 +72,91 @@ k_vbuild(int nw, int G, int MM, int xs, int xbs, double sqrt_tau, const double* 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int g = lane >> 4, c = lane & 15;
   const int wh = wave >> 1, eh = wave & 1;          // walker half, entry half
-  const int wb = blockIdx.y * VB_W, eb = blockIdx.x * E;
-  // global -> register staging: thread (j, w) takes walker w's AV consecutive
-  // vectors AV j .. AV j + AV - 1 of the chunk (consecutive lanes on consecutive
-  // walkers, so the LDS stores are conflict-free), and BV L entries, e fastest
-  constexpr int AV = VB_KC * VB_W / 256;            // (walker, k) pairs per thread
+  const int wb = blockIdx.y * W, eb = blockIdx.x * E;
+  // global -> register staging: VB_KC / AV consecutive lanes take one walker's vectors of
+  // the chunk, AV consecutive ones each (a wavefront reads few rows, whole 128 bytes of
+  // each), and every thread BV L entries, e fastest.  Column w of row k of the staged c
+  // is w ^ csw(k), so that the lanes of one walker store to different banks.
+  constexpr int AV = VB_KC * W / 256;               // (walker, k) pairs per thread
   constexpr int BV = VB_KC * E / 256;               // L entries per thread
-  static_assert(VB_KC * VB_W % 256 == 0 && VB_KC * E % 256 == 0, "whole chunks per thread");
-  const int wl = tid % VB_W, kj = AV * (tid / VB_W);
-  T ra[NA][AV], rb[BV];
+  static_assert(VB_KC * W % 512 == 0 && VB_KC * E % 256 == 0, "whole chunks per thread");
+  auto csw = [](int k) { return 16 * (k >> 2) & (W - 1); };
+  const int wl = tid / (VB_KC / AV), kj = AV * (tid % (VB_KC / AV));
+  const bool okw = wb + wl < nw;
+  const bool inner = wb + W <= nw && eb + E <= MM;  // no walker or entry past the end
+  const unsigned lo = (tid / E) * (unsigned)MM + tid % E;
+  const double* xw = xi + (size_t)min(wb + wl, nw - 1) * xs;
+  const double* xbw = XB ? xbar + (size_t)min(wb + wl, nw - 1) * xbs * 2 : nullptr;
+  dx2_a8 rx[AV / 2], rb[XB ? AV : 1];
+  double rl[BV];
   auto gload = [&](int k0) {
+    if (k0 + VB_KC <= G) {  // a whole chunk
+#pragma unroll
+      for (int i = 0; i < AV / 2; ++i)
+        rx[i] = *reinterpret_cast<const dx2_a8*>(xw + k0 + kj + 2 * i);
+      if constexpr (XB)
+#pragma unroll
+        for (int i = 0; i < AV; ++i)
+          rb[i] = *reinterpret_cast<const dx2_a8*>(xbw + (size_t)(k0 + kj + i) * 2);
+    } else {
+#pragma unroll
+      for (int i = 0; i < AV; ++i) {
+        const int kc = min(k0 + kj + i, G - 1);
+        rx[i / 2][i % 2] = xw[kc];
+        if constexpr (XB) rb[i] = *reinterpret_cast<const dx2_a8*>(xbw + (size_t)kc * 2);
+      }
+    }
+    if (inner && k0 + VB_KC <= G) {
+      const double* Lc = L + (size_t)k0 * MM + eb;
+#pragma unroll
+      for (int i = 0; i < BV; ++i) rl[i] = Lc[lo + (256 / E) * i * (unsigned)MM];
+    } else {
+#pragma unroll
+      for (int i = 0; i < BV; ++i) {
+        const int q = tid + 256 * i;
+        rl[i] = L[(size_t)min(k0 + q / E, G - 1) * MM + min(eb + q % E, MM - 1)];
+      }
+    }
+    AFQMC_KEEP_AHEAD();
+  };
+  auto put = [&](T* sa, int k0, auto whole) {
+    constexpr bool in = decltype(whole)::value;  // nothing to mask
+    T* sb = sa + CA;
 #pragma unroll
     for (int i = 0; i < AV; ++i) {
-      const int k = k0 + kj + i, w = wb + wl;
-      const bool ok = k < G && w < nw;
-      const int kc = min(k, G - 1), wc = min(w, nw - 1);
-      const double x = xi[(size_t)wc * xs + kc];
+      const int k = kj + i, col = wl ^ csw(k);
+      const bool ok = in || (okw && k0 + k < G);
+      const double x = rx[i / 2][i % 2];
       if constexpr (XB) {
-        const double br = xbar[((size_t)wc * xbs + kc) * 2], bi = xbar[((size_t)wc * xbs + kc) * 2 + 1];
-        ra[0][i] = (T)keep_if(x - br, ok);
-        ra[1][i] = (T)keep_if(-bi, ok);
+        sa[k * SAW + col] = (T)keep_if(x - rb[i][0], ok);
+        sa[(VB_KC + k) * SAW + col] = (T)keep_if(-rb[i][1], ok);
       } else {
-        ra[0][i] = (T)keep_if(x, ok);
+        sa[k * SAW + col] = (T)keep_if(x, ok);
       }
     }
 #pragma unroll
     for (int i = 0; i < BV; ++i) {
-      const int q = tid + 256 * i, k = k0 + q / E, e = eb + q % E;
-      const bool ok = k < G && e < MM;
-      rb[i] = (T)keep_if(L[(size_t)min(k, G - 1) * MM + min(e, MM - 1)], ok);
-    }
-  };
-  auto sstore = [&](int buf) {
-    T* sa = sbuf + buf * CH;
-    T* sb = sa + CA;
-#pragma unroll
-    for (int i = 0; i < AV; ++i)
-#pragma unroll
-      for (int p = 0; p < NA; ++p) sa[(p * VB_KC + kj + i) * SAW + wl] = ra[p][i];
-#pragma unroll
-    for (int i = 0; i < BV; ++i) {
       const int q = tid + 256 * i;
-      sb[(q / E) * SBE + q % E] = rb[i];
+      sb[(q / E) * SBE + q % E] =
+          (T)keep_if(rl[i], in || (k0 + q / E < G && eb + q % E < MM));
     }
   };
-  acc_t acc[NA][2][ET];
+  auto sstore = [&](int buf, int k0) {
+    if (inner && k0 + VB_KC <= G)
+      put(sbuf + buf * CH, k0, std::true_type{});
+    else
+      put(sbuf + buf * CH, k0, std::false_type{});
+  };
+  acc_t acc[NA][WT][ET];
 #pragma unroll
   for (int p = 0; p < NA; ++p)
 #pragma unroll
-    for (int wt = 0; wt < 2; ++wt)
+    for (int wt = 0; wt < WT; ++wt)
 #pragma unroll
       for (int et = 0; et < ET; ++et) acc[p][wt][et] = mm::zero();
   const int nch = (G + VB_KC - 1) / VB_KC;
   gload(0);
-  sstore(0);
+  sstore(0, 0);
   __syncthreads();
   for (int ch = 0; ch < nch; ++ch) {
     if (ch + 1 < nch) gload((ch + 1) * VB_KC);
@@ -126,31 +165,31 @@ k_vbuild(int nw, int G, int MM, int xs, int xbs, double sqrt_tau, const double* 
 #pragma unroll
     for (int ks = 0; ks < VB_KC / 4; ++ks) {
       const int k = 4 * ks + g;
-      T a[NA][2], b[ET];
+      T a[NA][WT], b[ET];
 #pragma unroll
       for (int p = 0; p < NA; ++p)
 #pragma unroll
-        for (int wt = 0; wt < 2; ++wt) a[p][wt] = sa[(p * VB_KC + k) * SAW + 32 * wh + 16 * wt + c];
+        for (int wt = 0; wt < WT; ++wt) a[p][wt] = sa[(p * VB_KC + k) * SAW + ((16 * WT * wh + 16 * wt + c) ^ csw(4 * ks))];
 #pragma unroll
       for (int et = 0; et < ET; ++et) b[et] = sb[k * SBE + (E / 2) * eh + 16 * et + c];
 #pragma unroll
       for (int p = 0; p < NA; ++p)
 #pragma unroll
-        for (int wt = 0; wt < 2; ++wt)
+        for (int wt = 0; wt < WT; ++wt)
 #pragma unroll
           for (int et = 0; et < ET; ++et) acc[p][wt][et] = mm::fma(a[p][wt], b[et], acc[p][wt][et]);
     }
     // the other buffer was last read in the previous chunk, before its barrier
-    if (ch + 1 < nch) sstore((ch + 1) & 1);
+    if (ch + 1 < nch) sstore((ch + 1) & 1, (ch + 1) * VB_KC);
     __syncthreads();
   }
 #pragma unroll
-  for (int wt = 0; wt < 2; ++wt)
+  for (int wt = 0; wt < WT; ++wt)
 #pragma unroll
     for (int et = 0; et < ET; ++et)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int w = wb + 32 * wh + 16 * wt + mm::row(g, r), e = eb + (E / 2) * eh + 16 * et + c;
+        const int w = wb + 16 * WT * wh + 16 * wt + mm::row(g, r), e = eb + (E / 2) * eh + 16 * et + c;
         if (RO) {
           if (w < nw && e < MM) vmat[(size_t)w * MM + e] = sqrt_tau * (double)acc[0][wt][et][r];
         } else if (w < nw && e < MM) {
@@ -353,19 +392,32 @@ k_weight(int nw, int P, int G, double dtau, double e_shift, int weight_mode,
 // reduced-precision walker propagation: mixed-precision contexts with real trials
 bool prop_f32(const afqmc_ctx_s* c) { return c->precision != AFQMC_PREC_FP64 && !c->ctrial; }
 
-template <typename T, bool XB, bool RO = false>
-hipError_t vb_launch(const afqmc_ctx_s* c, int n, int G, int MM, int xs, int xbs, double sqrt_s,
+template <typename T, int WT, bool XB, bool RO>
+hipError_t vb_launch_w(const afqmc_ctx_s* c, int n, int G, int MM, int xs, int xbs, double sqrt_s,
                      const double* L, const double* xi, const double* xbar, double* vmat) {
-  const size_t lds = vb_lds_bytes<T, XB>();
+  typedef VbShape<T, WT> Sh;
+  const size_t lds = vb_lds_bytes<T, WT, XB>();
   static_assert(!RO || !XB, "real output: no xbar");
-  auto kern = k_vbuild<T, XB, RO>;
+  auto kern = k_vbuild<T, WT, XB, RO>;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)lds);
   if (e != hipSuccess) return e;
-  const dim3 grid((MM + VbShape<T>::E - 1) / VbShape<T>::E, (n + VB_W - 1) / VB_W);
+  const dim3 grid((MM + Sh::E - 1) / Sh::E, (n + Sh::W - 1) / Sh::W);
   hipLaunchKernelGGL(kern, grid, dim3(256), lds, c->stream, n, G, MM, xs, xbs, sqrt_s, L, xi, xbar,
                      vmat);
   return hipGetLastError();
+}
+
+template <typename T, bool XB, bool RO = false>
+hipError_t vb_launch(const afqmc_ctx_s* c, int n, int G, int MM, int xs, int xbs, double sqrt_s,
+                     const double* L, const double* xi, const double* xbar, double* vmat) {
+  // 64 walkers a workgroup where that makes two workgroups for every CU, else 32.  128
+  // walkers of M = 64 (128 workgroups of 64): 39 us with 64, 23 with 32; 512 walkers (512):
+  // 54 and 62.
+  const long wide = (long)((MM + VbShape<T, 2>::E - 1) / VbShape<T, 2>::E) * ((n + 63) / 64);
+  if (wide < 512)
+    return vb_launch_w<T, 1, XB, RO>(c, n, G, MM, xs, xbs, sqrt_s, L, xi, xbar, vmat);
+  return vb_launch_w<T, 2, XB, RO>(c, n, G, MM, xs, xbs, sqrt_s, L, xi, xbar, vmat);
 }
 
 // The V and U builds of BF16 contexts on the workgroup kernels, on split-BF16
