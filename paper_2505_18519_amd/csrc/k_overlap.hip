@@ -1,176 +1,177 @@
 // Overlap, log-determinant and Green's function of every (walker, path) pair
 // (Sec. III.A, Eqs. ratio-update-phi and sign-path; Theta feeds Eq. local-obs).
 //
-// One wavefront per path handles both spins:
-//  1. A^s = Phi_T^T phi^s (N x N complex) on the FP64 matrix cores, operands
-//     read straight from HBM (real trial times the re / im parts of phi);
-//  2. LU with partial pivoting, one lane per row (lanes 0-15 spin up, 16-31
-//     spin down), pivot rows found by a 16-lane max reduction over DPP moves
-//     (largest |a|^2, lowest row on ties) and broadcast by lane shuffles
-//     instead of swapped;
+// One wavefront handles two paths, both spins of each, 16 lanes (rows) apiece:
+//  1. A^s = Phi_T^T phi^s (N x N complex) on the FP64 matrix cores, one path after the
+//     other, operands read straight from HBM (real trial times the re / im parts of phi);
+//  2. elimination with partial pivoting, one lane per row, pivot rows found by a
+//     16-lane max over DPP moves and a ballot (largest |a|^2, lowest row on ties)
+//     and broadcast by lane shuffles instead of swapped;
 //     det = parity(perm) prod u_kk, accumulated as a scaled complex product;
-//  3. optionally Theta^s = phi^s (A^s)^{-1}: lanes (spin, j) solve the unit rows
-//     e_j X^s = e_j (A^s)^{-1} with the factors (z U = e_j, v L = z,
-//     X[j][perm[k]] = v[k]), X^s replaces the factors in LDS, and
+//  3. with Theta or the Green's function diagonal requested the elimination is
+//     Gauss-Jordan in place, which leaves X^s = (A^s)^{-1} in the rows: X^s goes to LDS,
 //     Theta^s = phi^s X^s runs on the matrix cores (four real products per
-//     spin), stored as whole 16-byte complex entries along each row;
-//     with the Green's function diagonal Re (G_up + G_dn)_mm =
-//     Re sum_s sum_n Theta^s_mn Phi_T,mn requested, one lane per orbital row m
-//     solves x (A^s)^{-1} for its row of phi instead.
+//     spin), is stored as whole 16-byte complex entries along each row, and the
+//     diagonal Re (G_up + G_dn)_mm = Re sum_s sum_n Theta^s_mn Phi_T,mn is summed from
+//     its tiles.
 // A zero pivot marks the path singular: l = -inf + 0i and Theta = 0, diag = 0.
 // A non-finite overlap entry gives l = NaN + NaN i (Theta and diag 0).
+//
+// The elimination is a loop: after a step every row moves up one register, so that the
+// pivot column is always register 0 and one step's code serves all.  Unrolled over columns
+// and steps it was 82 KB of code, past the instruction cache (64 KB for two CUs), and the
+// passes over it set the time; now 5 to 11 KB.  Two paths fill the wavefront's 64 lanes.
+// Bound by the serial chain of a step (pivot search, reciprocal, broadcasts), with Theta also
+// by its writes.  Measured, before and now, log-overlaps / with Theta: M = 64, N = 16, 4096
+// paths 58 -> 40 / 111 -> 79 us; M = 48, N = 12, 4000 paths 49 -> 28 / 85 -> 55; M = 16,
+// N = 8, 300 paths 16 -> 10 / 24 -> 14; M = 8, N = 2, 512 paths 9.6 -> 9.8 / 13.2 -> 10.6.
 #include "afqmc_internal.h"
 #include "dev_common.h"
 
 namespace {
 
 constexpr int OV_WAVES = 4;
-constexpr int NT = 16;  // N <= 16
 
-template <int MT>
-__global__ void __launch_bounds__(OV_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
+// NC: columns of a row in registers (N <= NC); INV: Theta or the diagonal requested
+template <int NC, bool INV>
+__global__ void __launch_bounds__(OV_WAVES * 64, 2)
 k_overlap(int n_samples, int P, int M, int N, const double* __restrict__ phi,
           const double* __restrict__ phiT, double* __restrict__ logov, double* __restrict__ theta,
           double* __restrict__ gdiag) {
-  __shared__ double s_lu[OV_WAVES][2][NT][NT][2];  // LU rows in pivot order
-  __shared__ int s_perm[OV_WAVES][2][NT];
+  __shared__ double s_lu[OV_WAVES][4][NC][NC + 1][2];  // [path, spin]: A, then X
+  __shared__ int s_perm[OV_WAVES][4][NC];
 
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
   const int g = lane >> 4, c = lane & 15;
-  const int s = blockIdx.x * OV_WAVES + wave;
-  if (s >= n_samples) return;  // no block-level barriers below
-  const int w = s / P;
-  const double* pT = phiT + (size_t)s * M * N;
-  const double* pw = phi + (size_t)w * 2 * M * N * 2;
+  const int s0 = (blockIdx.x * OV_WAVES + wave) * 2;
+  if (s0 >= n_samples) return;  // no block-level barriers below
+  const auto fence = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  };
 
-  // 1. A^s via MFMA: tiles (re up, im up, re dn, im dn); lane holds A[g+4r][c]
-  dx4 acc[4] = {dx4_zero(), dx4_zero(), dx4_zero(), dx4_zero()};
+  // 1. A^s: tiles (re up, im up, re dn, im dn); lane holds A[g+4r][c].  A lone last path
+  // takes both places.
+#pragma unroll 1
+  for (int h = 0; h < 2; ++h) {
+    const int s = min(s0 + h, n_samples - 1);
+    const double* pT = phiT + (size_t)s * M * N;
+    const double* pw = phi + (size_t)(s / P) * 2 * M * N * 2;
+    dx4 acc[4] = {dx4_zero(), dx4_zero(), dx4_zero(), dx4_zero()};
 #pragma unroll 4
-  for (int q = 0; q < MT / 4; ++q) {
-    const int m = 4 * q + g;
-    const bool okm = m < M, okc = c < N;
-    const double a = (okm && okc) ? pT[m * N + c] : 0.0;
+    for (int q = 0; q < (M + 3) / 4; ++q) {
+      const int m = 4 * q + g;
+      const bool ok = m < M && c < N;
+      const size_t e = (size_t)min(m, M - 1) * N + min(c, N - 1);
+      const double a = keep_if(pT[e], ok);
 #pragma unroll
-    for (int sp = 0; sp < 2; ++sp) {
-      double br = 0.0, bi = 0.0;
-      if (okm && okc) {
-        const double* src = pw + ((size_t)(sp * M + m) * N + c) * 2;
-        br = src[0];
-        bi = src[1];
+      for (int sp = 0; sp < 2; ++sp) {
+        const double2 x = *reinterpret_cast<const double2*>(pw + ((size_t)sp * M * N + e) * 2);
+        acc[2 * sp] = mfma_f64(a, keep_if(x.x, ok), acc[2 * sp]);
+        acc[2 * sp + 1] = mfma_f64(a, keep_if(x.y, ok), acc[2 * sp + 1]);
       }
-      acc[2 * sp] = mfma_f64(a, br, acc[2 * sp]);
-      acc[2 * sp + 1] = mfma_f64(a, bi, acc[2 * sp + 1]);
     }
+#pragma unroll
+    for (int sp = 0; sp < 2; ++sp)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (NC == 16 || (g + 4 * r < NC && c < NC)) {
+          s_lu[wave][2 * h + sp][g + 4 * r][c][0] = acc[2 * sp][r];
+          s_lu[wave][2 * h + sp][g + 4 * r][c][1] = acc[2 * sp + 1][r];
+        }
   }
-  // stage A rows through LDS (reuse the LU buffer as the A buffer)
-#pragma unroll
-  for (int sp = 0; sp < 2; ++sp)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      s_lu[wave][sp][g + 4 * r][c][0] = acc[2 * sp][r];
-      s_lu[wave][sp][g + 4 * r][c][1] = acc[2 * sp + 1][r];
-    }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  fence();
 
-  // 2. LU: lane = (sp, i) for lanes < 32
-  const int sp = (lane >> 4) & 1;
+  // 2. elimination: lane = (path, spin, row i)
   const int i = c;
-  cplx a[NT];
+  cplx a[NC];
 #pragma unroll
-  for (int j = 0; j < NT; ++j) a[j] = cmk(s_lu[wave][sp][i][j][0], s_lu[wave][sp][i][j][1]);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-
-  bool used = (i >= N) || (lane >= 32);
+  for (int j = 0; j < NC; ++j) {
+    a[j] = cmk(s_lu[wave][g][min(i, NC - 1)][j][0], s_lu[wave][g][min(i, NC - 1)][j][1]);
+    if (NC < 16 && i >= NC) a[j] = cmk(0.0, 0.0);
+  }
+  fence();
   // a non-finite entry of either spin's overlap matrix makes l NaN (a
   // numerical event, not a singular path)
-  bool nonfinite = false;
-  if (!used) {
+  double nf = 0.0;
 #pragma unroll
-    for (int k = 0; k < NT; ++k)
-      if (k < N) nonfinite |= !(isfinite(a[k].re) && isfinite(a[k].im));
-  }
-  const bool nf_any = __ballot(nonfinite) != 0;
+  for (int j = 0; j < NC; ++j) nf = fma(a[j].re, 0.0, fma(a[j].im, 0.0, nf));
+  const bool nf_any = ((__ballot(nf != 0.0) >> (lane & 32)) & 0xffffffffull) != 0;  // the path's
+  bool used = i >= N;
   int mystep = -1;
-  int perm[NT];
+  cplx scale = cmk(0.0, 0.0);  // 1 / pivot of this lane's row
   // det = prod of pivots, kept as a complex mantissa times 2^pexp so that it
   // neither overflows nor needs a logarithm per step
   cplx pprod = cmk(1.0, 0.0);
-  int pexp = 0;
+  int pexp = 0, inv = 0;
+  unsigned done = 0;  // pivot rows so far
   bool singular = false;
-  const int base = lane & ~15;  // first lane of my 16-lane group
-#pragma unroll
-  for (int k = 0; k < NT; ++k) {
-    if (k < N) {
-      // pivot: max |a_ik|^2 over unused rows, lowest i on ties
-      // NaN entries count as zero so that the reduction order is total and
-      // every lane of the group agrees on the pivot
-      double v = used ? -1.0 : cabs2(a[k]);
-      if (!used && !(v >= 0.0)) v = 0.0;
-      int idx = used ? 1000 : i;
-      // across the 16-lane row with DPP moves (VALU latency, no LDS round trip):
-      // partner lane xor 1, xor 2, then the mirrored quad, then the mirrored half
-      auto take = [&](double v2, int i2) {
-        if (v2 > v || (v2 == v && i2 < idx)) {
-          v = v2;
-          idx = i2;
-        }
-      };
-      take(dpp_f64<0xB1>(v), dpp_i32<0xB1>(idx));
-      take(dpp_f64<0x4E>(v), dpp_i32<0x4E>(idx));
-      take(dpp_f64<0x141>(v), dpp_i32<0x141>(idx));
-      take(dpp_f64<0x140>(v), dpp_i32<0x140>(idx));
-      const int prow = idx;  // uniform within the group
-      perm[k] = prow;
-      const int src = base + (prow & 15);
-      const cplx piv = cmk(__shfl(a[k].re, src, 64), __shfl(a[k].im, src, 64));
-      if (!(v > 0.0)) singular = true;
-      if (i == prow && !used) {
-        used = true;
-        mystep = k;
-      }
-      pprod = cmul(pprod, piv);
-      {
-        const double mx = fmax(fabs(pprod.re), fabs(pprod.im));
-        if (mx > 0.0 && isfinite(mx)) {
-          const int ex = ilogb(mx);
-          pprod = cscale(pprod, ldexp(1.0, -ex));
-          pexp += ex;
-        }
-      }
-      cplx l = cmk(0.0, 0.0);
-      if (!used && !singular) {
-        l = cmul(a[k], crecip(piv));  // the pivot's reciprocal: one real division
-        a[k] = l;
-      }
-#pragma unroll
-      for (int j = k + 1; j < NT; ++j) {
-        const cplx pj = cmk(__shfl(a[j].re, src, 64), __shfl(a[j].im, src, 64));
-        if (!used && !singular) a[j] = cfms(a[j], l, pj);
-      }
+  // step k on the first W registers.  INV: Gauss-Jordan in place; column k of the
+  // inverse takes the place of the pivot column, and pivot rows stay unscaled (row
+  // `scale` times the registers) as every update is linear in the row it changes.
+  auto step = [&](auto WW, int k) {
+    constexpr int W = decltype(WW)::value;
+    // NaN entries count as zero so that the order is total and every lane of the
+    // group agrees on the pivot
+    double v = used ? -1.0 : cabs2(a[0]);
+    if (!used && !(v >= 0.0)) v = 0.0;
+    double vm = fmax(v, dpp_f64<0xB1>(v));
+    vm = fmax(vm, dpp_f64<0x4E>(vm));
+    vm = fmax(vm, dpp_f64<0x141>(vm));
+    vm = fmax(vm, dpp_f64<0x140>(vm));
+    const unsigned cand = (unsigned)(__ballot(!used && v == vm) >> (lane & 48)) & 0xffffu;
+    const int prow = __builtin_ctz(cand | 0x10000u) & 15;  // uniform within the group
+    inv += __builtin_popcount(done >> prow);
+    done |= 1u << prow;
+    const int src = (lane & 48) + prow;
+    const cplx piv = cmk(__shfl(a[0].re, src, 64), __shfl(a[0].im, src, 64));
+    if (!(vm > 0.0)) singular = true;
+    const bool mine = i == prow;
+    if (mine) {
+      used = true;
+      mystep = k;
     }
+    pprod = cmul(pprod, piv);
+    const double mx = fmax(fabs(pprod.re), fabs(pprod.im));
+    if (mx > 0.0 && isfinite(mx)) {
+      const int ex = ilogb(mx);
+      pprod = cscale(pprod, ldexp(1.0, -ex));
+      pexp += ex;
+    }
+    const cplx rp = crecip(piv);  // the pivot's reciprocal: one real division
+    if (INV && mine) scale = rp;
+    cplx l = cmul(a[0], rp);
+    if (mine || singular || (!INV && used)) l = cmk(0.0, 0.0);
+#pragma unroll
+    for (int j = 0; j + 1 < W; ++j) {
+      const cplx pj = cmk(__shfl(a[j + 1].re, src, 64), __shfl(a[j + 1].im, src, 64));
+      a[j] = cfms(a[j + 1], l, pj);
+    }
+    if (INV) a[W - 1] = mine ? cmk(1.0, 0.0) : cmk(-l.re, -l.im);
+  };
+  if constexpr (INV) {
+#pragma unroll 1
+    for (int k = 0; k < N; ++k) step(std::integral_constant<int, NC>{}, k);
+  } else {
+    int k = 0;
+    unrolled<NC / 8>([&](auto I) {  // N - k columns are left: W, W - 8
+      constexpr int W = NC - 8 * decltype(I)::value;
+#pragma unroll 1
+      for (; k < N - W + 8; ++k) step(std::integral_constant<int, W>{}, k);
+    });
   }
-  // parity of the step -> row permutation (uniform per group)
-  int inv = 0;
-#pragma unroll
-  for (int x = 0; x < NT; ++x)
-#pragma unroll
-    for (int y = x + 1; y < NT; ++y)
-      if (y < N && perm[x] > perm[y]) ++inv;
-  double logabs = 0.5 * log(cabs2(pprod)) + (double)pexp * M_LN2;
-  double argsum = atan2(pprod.im, pprod.re) + ((inv & 1) ? M_PI : 0.0);
+  const double logabs = 0.5 * log(cabs2(pprod)) + (double)pexp * M_LN2;
+  const double argsum = atan2(pprod.im, pprod.re) + ((inv & 1) ? M_PI : 0.0);
 
-  // both spins' results to lane 0 of the wave
-  const double la_dn = __shfl(logabs, 16, 64), ar_dn = __shfl(argsum, 16, 64);
-  const int sing_dn = __shfl((int)singular, 16, 64);
-  const int sing_up = __shfl((int)singular, 0, 64);
-  const bool sing_any = sing_up || sing_dn;
-  if (lane == 0) {
-    double* o = logov + (size_t)s * 2;
+  // both spins' results to the lanes of the path's first spin
+  const double la_dn = __shfl(logabs, (lane & 32) + 16, 64);
+  const double ar_dn = __shfl(argsum, (lane & 32) + 16, 64);
+  const bool sing_any =
+      (__shfl((int)singular, lane & 32, 64) | __shfl((int)singular, (lane & 32) + 16, 64)) != 0;
+  if ((lane & 31) == 0 && s0 + (lane >> 5) < n_samples) {
+    double* o = logov + (size_t)(s0 + (lane >> 5)) * 2;
     if (nf_any) {
       o[0] = __builtin_nan("");
       o[1] = __builtin_nan("");
@@ -182,180 +183,112 @@ k_overlap(int n_samples, int P, int M, int N, const double* __restrict__ phi,
       o[1] = argsum + ar_dn;
     }
   }
-  if (theta == nullptr && gdiag == nullptr) return;
+  if constexpr (!INV) return;
 
-  double* th = theta ? theta + (size_t)s * 2 * M * N * 2 : nullptr;
-  double* gd = gdiag ? gdiag + (size_t)s * M : nullptr;
-  if (sing_any || nf_any) {
-    if (th)
-      for (int q = lane; q < 2 * M * N * 2; q += 64) th[q] = 0.0;
-    if (gd)
-      for (int q = lane; q < M; q += 64) gd[q] = 0.0;
-    return;
+  // 3. X^s = (A^s)^{-1}: the row of step k is X's row k, and register NC - N + m its column
+  //    perm[m]; the rest is zero
+  const unsigned long long deadm = __ballot(sing_any || nf_any);
+  if (mystep >= 0) s_perm[wave][g][mystep] = i;
+  if (i < NC)
+#pragma unroll
+    for (int j = 0; j < NC; ++j) s_lu[wave][g][i][j][0] = s_lu[wave][g][i][j][1] = 0.0;
+  fence();
+  if (mystep >= 0) {
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const int m = j - (NC - N);
+      if (m >= 0) {
+        const cplx x = cmul(a[j], scale);
+        const int col = s_perm[wave][g][m];
+        s_lu[wave][g][mystep][col][0] = x.re;
+        s_lu[wave][g][mystep][col][1] = x.im;
+      }
+    }
   }
-  // LU rows in step order, and the permutation, to LDS
-  if (lane < 32 && i < N && mystep >= 0) {
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      s_lu[wave][sp][mystep][j][0] = a[j].re;
-      s_lu[wave][sp][mystep][j][1] = a[j].im;
+  fence();
+  // 4. Theta^s = phi^s X^s on the matrix cores: A[c][g] = phi[16t + c][4q + g],
+  //    B[g][c] = X[4q + g][c]; the lane holds Theta[16t + g + 4r][c]
+#pragma unroll 1
+  for (int h = 0; h < 2; ++h) {
+    const int s = s0 + h;
+    if (s >= n_samples) break;
+    double* th = theta ? theta + (size_t)s * 2 * M * N * 2 : nullptr;
+    double* gd = gdiag ? gdiag + (size_t)s * M : nullptr;
+    if ((deadm >> (32 * h)) & 1) {
+      if (th)
+        for (int q = lane; q < 2 * M * N * 2; q += 64) th[q] = 0.0;
+      if (gd)
+        for (int q = lane; q < M; q += 64) gd[q] = 0.0;
+      continue;
     }
-  }
-  if (lane < 32 && i < N && mystep >= 0) s_perm[wave][sp][mystep] = i;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-
-  if (gdiag == nullptr) {
-    // 3. X^s = (A^s)^{-1}: lane (spin, j) < 32 solves e_j X = e_j A^{-1} with the
-    //    factors (z U = e_j, v L = z, X[j][perm[k]] = v[k]); rows j >= N stay zero
-    const int jr = c, spn = (lane >> 4) & 1;
-    const bool solver = lane < 32 && jr < N;
-    cplx x[NT];
+    const double* pT = phiT + (size_t)s * M * N;
+    const double* pw = phi + (size_t)(s / P) * 2 * M * N * 2;
+    double xr[2][NC / 4], xi[2][NC / 4];
 #pragma unroll
-    for (int j = 0; j < NT; ++j) x[j] = cmk(j == jr ? 1.0 : 0.0, 0.0);
-    if (solver) {
+    for (int sp = 0; sp < 2; ++sp)
 #pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        if (j < N) {
-          cplx acc2 = x[j];
-#pragma unroll
-          for (int k = 0; k < j; ++k)
-            acc2 = cfms(acc2, x[k], cmk(s_lu[wave][spn][k][j][0], s_lu[wave][spn][k][j][1]));
-          x[j] = cdiv(acc2, cmk(s_lu[wave][spn][j][j][0], s_lu[wave][spn][j][j][1]));
-        }
+      for (int q = 0; q < NC / 4; ++q) {  // columns from N on are not used
+        xr[sp][q] = s_lu[wave][2 * h + sp][4 * q + g][min(c, NC - 1)][0];
+        xi[sp][q] = s_lu[wave][2 * h + sp][4 * q + g][min(c, NC - 1)][1];
       }
+#pragma unroll 1
+    for (int t = 0; t < (M + 15) / 16; ++t) {
+      double gs[4] = {0.0, 0.0, 0.0, 0.0};
+      const int m = 16 * t + c;
+      double2 v[2][NC / 4];
 #pragma unroll
-      for (int j = NT - 1; j >= 0; --j) {
-        if (j < N) {
-          cplx acc2 = x[j];
+      for (int sp = 0; sp < 2; ++sp)
 #pragma unroll
-          for (int k = j + 1; k < NT; ++k)
-            if (k < N)
-              acc2 = cfms(acc2, x[k], cmk(s_lu[wave][spn][k][j][0], s_lu[wave][spn][k][j][1]));
-          x[j] = acc2;
-        }
-      }
-    }
-    int pcol[NT];
-#pragma unroll
-    for (int k = 0; k < NT; ++k) pcol[k] = min(max(s_perm[wave][spn][k], 0), NT - 1);
-    // every lane of the wave has issued its factor reads: X replaces the factors in LDS
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    if (lane < 32) {
-#pragma unroll
-      for (int k = 0; k < NT; ++k) {  // unused columns first, then the solved row
-        s_lu[wave][spn][jr][k][0] = 0.0;
-        s_lu[wave][spn][jr][k][1] = 0.0;
-      }
-      if (solver) {
-#pragma unroll
-        for (int k = 0; k < NT; ++k)
-          if (k < N) {
-            s_lu[wave][spn][jr][pcol[k]][0] = x[k].re;
-            s_lu[wave][spn][jr][pcol[k]][1] = x[k].im;
-          }
-      }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    // 4. Theta^s = phi^s X^s on the matrix cores: A[c][g] = phi[16t + c][4q + g],
-    //    B[g][c] = X[4q + g][c]; the lane holds Theta[16t + g + 4r][c]
-#pragma unroll
-    for (int spin = 0; spin < 2; ++spin) {
-      double xr[4], xi[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        xr[q] = s_lu[wave][spin][4 * q + g][c][0];
-        xi[q] = s_lu[wave][spin][4 * q + g][c][1];
-      }
-#pragma unroll
-      for (int t = 0; t < MT / 16; ++t) {
-        dx4 tr = dx4_zero(), ti = dx4_zero();
-        const int m = 16 * t + c;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < NC / 4; ++q) {
           const int n = 4 * q + g;
-          double2 v = make_double2(0.0, 0.0);
-          if (m < M && n < N)
-            v = *reinterpret_cast<const double2*>(pw + ((size_t)(spin * M + m) * N + n) * 2);
-          tr = mfma_f64(v.x, xr[q], tr);
-          tr = mfma_f64(-v.y, xi[q], tr);
-          ti = mfma_f64(v.x, xi[q], ti);
-          ti = mfma_f64(v.y, xr[q], ti);
+          const double2 e = *reinterpret_cast<const double2*>(
+              pw + ((size_t)(sp * M + min(m, M - 1)) * N + min(n, N - 1)) * 2);
+          const bool ok = m < M && n < N;
+          v[sp][q] = make_double2(keep_if(e.x, ok), keep_if(e.y, ok));
+        }
+#pragma unroll
+      for (int sp = 0; sp < 2; ++sp) {
+        dx4 tr = dx4_zero(), ti = dx4_zero();
+#pragma unroll
+        for (int q = 0; q < NC / 4; ++q) {
+          tr = mfma_f64(v[sp][q].x, xr[sp][q], tr);
+          tr = mfma_f64(-v[sp][q].y, xi[sp][q], tr);
+          ti = mfma_f64(v[sp][q].x, xi[sp][q], ti);
+          ti = mfma_f64(v[sp][q].y, xr[sp][q], ti);
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int mo = 16 * t + g + 4 * r;
-          if (mo < M && c < N)
-            *reinterpret_cast<double2*>(th + ((size_t)(spin * M + mo) * N + c) * 2) =
-                make_double2(tr[r], ti[r]);
+          if (mo < M && c < N) {
+            if (th)
+              *reinterpret_cast<double2*>(th + ((size_t)(sp * M + mo) * N + c) * 2) =
+                  make_double2(tr[r], ti[r]);
+            if (gd) gs[r] = fma(tr[r], pT[(size_t)mo * N + c], gs[r]);
+          }
         }
       }
-    }
-    return;
-  }
-
-  // 3. Theta rows with the Green's function diagonal: lane = orbital row m
-  for (int m0 = 0; m0 < M; m0 += 64) {
-    double gsum = 0.0;
-    for (int spin = 0; spin < 2; ++spin) {
-      const int m = m0 + lane;
-      if (m < M) {
-        cplx x[NT];
-        const double* src = pw + ((size_t)(spin * M + m) * N) * 2;
+      if (gd)  // sum over the columns: the 16 lanes of a row
 #pragma unroll
-        for (int j = 0; j < NT; ++j) x[j] = (j < N) ? cmk(src[2 * j], src[2 * j + 1]) : cmk(0, 0);
-        // z U = x  (forward in j)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) {
-          if (j < N) {
-            cplx acc2 = x[j];
-#pragma unroll
-            for (int k = 0; k < j; ++k)
-              acc2 = cfms(acc2, x[k], cmk(s_lu[wave][spin][k][j][0], s_lu[wave][spin][k][j][1]));
-            x[j] = cdiv(acc2, cmk(s_lu[wave][spin][j][j][0], s_lu[wave][spin][j][j][1]));
-          }
+        for (int r = 0; r < 4; ++r) {
+          double x = gs[r];
+          x += dpp_f64<0xB1>(x);
+          x += dpp_f64<0x4E>(x);
+          x += dpp_f64<0x141>(x);
+          x += dpp_f64<0x140>(x);
+          const int mo = 16 * t + g + 4 * r;
+          if (c == 0 && mo < M) gd[mo] = x;
         }
-        // v L = z  (backward in j, unit lower L_kj stored at row k, col j < k)
-#pragma unroll
-        for (int j = NT - 1; j >= 0; --j) {
-          if (j < N) {
-            cplx acc2 = x[j];
-#pragma unroll
-            for (int k = j + 1; k < NT; ++k)
-              if (k < N)
-                acc2 = cfms(acc2, x[k], cmk(s_lu[wave][spin][k][j][0], s_lu[wave][spin][k][j][1]));
-            x[j] = acc2;
-          }
-        }
-        double* dst = th ? th + ((size_t)(spin * M + m) * N) * 2 : nullptr;
-#pragma unroll
-        for (int k = 0; k < NT; ++k)
-          if (k < N) {
-            const int col = min(max(s_perm[wave][spin][k], 0), N - 1);
-            if (dst) {
-              dst[2 * col] = x[k].re;
-              dst[2 * col + 1] = x[k].im;
-            }
-            gsum = fma(x[k].re, pT[m * N + col], gsum);
-          }
-      }
     }
-    if (gd && m0 + lane < M) gd[m0 + lane] = gsum;
   }
 }
 
-template <int MT>
-hipError_t launch_mt(const afqmc_ctx_s* c, int nw, const double* phi, const double* phiT,
+template <int NC>
+hipError_t launch_nc(const afqmc_ctx_s* c, int nw, const double* phi, const double* phiT,
                      double* logov, double* theta, double* gdiag) {
   const int n = nw * c->P;
-  dim3 grid((n + OV_WAVES - 1) / OV_WAVES), block(OV_WAVES * 64);
-  hipLaunchKernelGGL(k_overlap<MT>, grid, block, 0, c->stream, n, c->P, c->M, c->N, phi, phiT,
-                     logov, theta, gdiag);
+  auto kern = theta != nullptr || gdiag != nullptr ? k_overlap<NC, true> : k_overlap<NC, false>;
+  hipLaunchKernelGGL(kern, dim3((n + 2 * OV_WAVES - 1) / (2 * OV_WAVES)), dim3(OV_WAVES * 64), 0,
+                     c->stream, n, c->P, c->M, c->N, phi, phiT, logov, theta, gdiag);
   return hipGetLastError();
 }
 
@@ -364,11 +297,7 @@ hipError_t launch_mt(const afqmc_ctx_s* c, int nw, const double* phi, const doub
 hipError_t launch_overlap(const afqmc_ctx_s* c, int nw, const double* phi, const double* phiT,
                           double* logov, double* theta, double* gdiag) {
   if (nw <= 0) return hipSuccess;
-  switch (c->MT) {
-    case 16: return launch_mt<16>(c, nw, phi, phiT, logov, theta, gdiag);
-    case 32: return launch_mt<32>(c, nw, phi, phiT, logov, theta, gdiag);
-    case 48: return launch_mt<48>(c, nw, phi, phiT, logov, theta, gdiag);
-    case 64: return launch_mt<64>(c, nw, phi, phiT, logov, theta, gdiag);
-    default: return hipErrorInvalidValue;
-  }
+  if (c->N > 16) return hipErrorInvalidValue;
+  return c->N <= 8 ? launch_nc<8>(c, nw, phi, phiT, logov, theta, gdiag)
+                   : launch_nc<16>(c, nw, phi, phiT, logov, theta, gdiag);
 }

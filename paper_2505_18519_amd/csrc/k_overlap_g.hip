@@ -327,12 +327,6 @@ hipError_t launch_g(const afqmc_ctx_s* c, int nw, const double* phi, const doubl
 hipError_t launch_overlap_g(const afqmc_ctx_s* c, int nw, const double* phi, const double* phiT,
                             double* logov, double* theta, double* gdiag) {
   if (nw <= 0) return hipSuccess;
-  // The FP32 and split-BF16 contractions round Theta to FP32 (two BF16): the inverse's last
-  // bits (1e-15) would move the rounding of about one entry in 10^7 (10^10), by 6e-8 (8e-6).
-  // A BF16 rounding is coarse enough (one entry in 10^12).
-  if ((c->precision == AFQMC_PREC_FP32 || c->precision == AFQMC_PREC_BF16X3) && !c->ctrial &&
-      theta != nullptr && gdiag == nullptr)
-    return launch_overlap_lu(c, nw, phi, phiT, logov, theta);
   switch ((c->N + 7) / 8) {
     case 1: return launch_g<8>(c, nw, phi, phiT, logov, theta, gdiag);
     case 2: return launch_g<16>(c, nw, phi, phiT, logov, theta, gdiag);

@@ -1,5 +1,5 @@
-"""The workgroup overlap kernels at the edges of their column counts (8, 16, .. 40), against
-the FP64 oracle: log-overlaps alone and with the Green's function, the diagonal, a
+"""The overlap kernels at the edges of their column counts (8, 16, .. 40), with an odd last
+path where a wavefront takes two, against the FP64 oracle: log-overlaps alone and with the Green's function, the diagonal, a
 path of zero overlap and one with an infinite entry.  Tolerance 1e-10, as for every
 FP64 overlap; the log-overlaps with and without Theta come from the same pivots
 and products and agree to 1e-13."""
@@ -16,9 +16,9 @@ pytestmark = pytest.mark.gpu
 
 TOL = 1e-10
 
-# (M, N): past M = 64 or N = 16
-SIZES = [(65, 1), (72, 7), (80, 8), (97, 9), (66, 16), (20, 17), (24, 24), (90, 25), (33, 32),
-         (129, 33), (160, 40)]
+# (M, N): up to and past M = 64, N = 16
+SIZES = [(1, 1), (8, 2), (17, 8), (30, 9), (64, 16), (63, 15), (65, 1), (72, 7), (80, 8), (97, 9), (66, 16),
+         (20, 17), (24, 24), (90, 25), (33, 32), (129, 33), (160, 40)]
 
 
 def dev(x):
