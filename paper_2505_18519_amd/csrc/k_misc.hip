@@ -207,54 +207,6 @@ k_estimator_corrected(int nw, int P, int Pr, const double* __restrict__ w,
   }
 }
 
-// Re-orthonormalisation by modified Gram-Schmidt applied twice, one 64-lane
-// workgroup per walker (lane = orbital row; M <= 64, N <= 16).  R_jj is the
-// norm of column j after both projection passes, hence real positive.
-__global__ void __launch_bounds__(64)
-k_qr(int nw, int P, int M, int N, double* __restrict__ phi, double* __restrict__ logov) {
-  constexpr int NTQ = 16;
-  const int w = blockIdx.x;
-  const int m = threadIdx.x;
-  double shift = 0.0;
-  for (int sp = 0; sp < 2; ++sp) {
-    double* base = phi + ((size_t)(w * 2 + sp) * M) * N * 2;
-    cplx q[NTQ];
-#pragma unroll
-    for (int j = 0; j < NTQ; ++j)
-      q[j] = (m < M && j < N) ? cmk(base[((size_t)m * N + j) * 2], base[((size_t)m * N + j) * 2 + 1])
-                              : cmk(0.0, 0.0);
-#pragma unroll
-    for (int j = 0; j < NTQ; ++j) {
-      if (j < N) {
-        cplx v = q[j];
-#pragma unroll
-        for (int pass = 0; pass < 2; ++pass)
-#pragma unroll
-          for (int k = 0; k < j; ++k) {
-            // h = q_k^H v
-            double hr = q[k].re * v.re + q[k].im * v.im;
-            double hi = q[k].re * v.im - q[k].im * v.re;
-            hr = wave_sum(hr);
-            hi = wave_sum(hi);
-            v = cfms(v, cmk(hr, hi), q[k]);
-          }
-        const double nrm = sqrt(wave_sum(cabs2(v)));
-        shift += log(nrm);
-        q[j] = cscale(v, 1.0 / nrm);
-      }
-    }
-    if (m < M)
-#pragma unroll
-      for (int j = 0; j < NTQ; ++j)
-        if (j < N) {
-          base[((size_t)m * N + j) * 2] = q[j].re;
-          base[((size_t)m * N + j) * 2 + 1] = q[j].im;
-        }
-  }
-  if (logov != nullptr)
-    for (int p = m; p < P; p += 64) logov[((size_t)w * P + p) * 2] -= shift;
-}
-
 __global__ void k_to_float(size_t n, const double* __restrict__ src, float* __restrict__ dst) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) dst[i] = (float)src[i];
@@ -357,12 +309,6 @@ hipError_t launch_estimator(const afqmc_ctx_s* c, int nw, const double* w, const
   return hipGetLastError();
 }
 
-hipError_t launch_qr(const afqmc_ctx_s* c, int nw, double* phi, double* logov) {
-  if (nw <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_qr, dim3(nw), dim3(64), 0, c->stream, nw, c->P, c->M, c->N, phi, logov);
-  return hipGetLastError();
-}
-
 hipError_t launch_to_float(const afqmc_ctx_s* c, size_t n, const double* src, float* dst) {
   hipLaunchKernelGGL(k_to_float, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, n, src,
                      dst);
@@ -412,99 +358,122 @@ hipError_t launch_zero_int(const afqmc_ctx_s* c, int n, int* p) {
 }
 
 // ---------------------------------------------------------------------------
-// Re-orthonormalisation for larger systems (M <= 160, N <= 40): classical
-// Gram-Schmidt applied twice (each column projected against all the previous
-// ones at once, then again), one workgroup of QW wavefronts (64 QW >= M) per
-// walker and spin, thread = orbital row, the columns in LDS.  The j inner
-// products h = Q_{<j}^H v of column j are summed by lane k of each wavefront
-// over that wavefront's 64 rows and the wavefronts' partial sums added through
-// LDS: three barriers per pass instead of one workgroup reduction per inner
-// product.  The rows in LDS are padded by one complex entry, so that the
-// threads' reads along their own rows fall on different banks.
+// Re-orthonormalisation (M <= 160, N <= 40): classical Gram-Schmidt applied twice (each
+// column projected against all the previous ones at once, then again), one workgroup
+// of QW wavefronts (64 QW >= M) per walker and spin (M <= 64, N <= 16: one of two wavefronts
+// per walker), thread = orbital row, the columns in LDS.  R_jj is the norm of column j after both
+// projection passes, hence real positive.  The j inner products h = Q_{<j}^H v of column j
+// are summed by lane k over its group's rows (KW lanes a group, so that half- and
+// quarter-wavefronts take rows of their own) and the groups' partial sums added through
+// LDS: three barriers per pass instead of one workgroup reduction per inner product.
+// The rows in LDS are padded by one complex entry, so that the threads' reads along their
+// own rows fall on different banks.
+// Bound by the reads of Q from LDS, twice a pass, and the serial columns.  Before (one group
+// a wavefront, sums by shuffles) and now: M = 72, N = 18, 700 walkers
+// 248 -> 126 us; M = 128, N = 32, 500 walkers 553 -> 360; and where one wavefront ran modified
+// Gram-Schmidt with two shuffle sums per inner product, M = 64, N = 16, 512 walkers
+// 146 -> 76 us.
 namespace {
 
-template <int QW>
-__global__ void __launch_bounds__(64 * QW)
+// sum over the wavefront, all 64 lanes active: DPP moves within each 16-lane row, then the
+// rows' sums by readlane
+__device__ __forceinline__ double wave_sum_full(double v) {
+  v += dpp_f64<0xB1>(v);
+  v += dpp_f64<0x4E>(v);
+  v += dpp_f64<0x141>(v);
+  v += dpp_f64<0x140>(v);
+  return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
+}
+
+// KW: lanes that take a column each in the inner products (N <= KW); the 64 / KW groups of a
+// wavefront take rows of their own.  BOTH: one workgroup does both spins, a wavefront each,
+// and shifts the log-overlaps itself.
+template <int QW, int KW, bool BOTH>
+__global__ void __launch_bounds__(BOTH ? 128 : 64 * QW)
 k_qr_g(int nw, int P, int M, int N, double* __restrict__ phi, double* __restrict__ logshift) {
   constexpr int QRG_T = 64 * QW;
-  extern __shared__ double sq[];           // [M][RS]: row m, N complex entries and a pad
-  __shared__ double s_v[QRG_T][2];         // the column being orthogonalised
-  __shared__ double s_hp[QW][64][2];       // per-wavefront partial inner products
-  __shared__ double s_h[64][2];            // h = Q_{<j}^H v
-  __shared__ double s_red[QW][2];
-  const int w = blockIdx.x, sp = blockIdx.y;
-  const int m = threadIdx.x, wave = m >> 6, lane = m & 63;
+  constexpr int GR = 64 / KW * QW;         // groups of rows
+  constexpr int NS = BOTH ? 2 : 1;         // spins
+  static_assert(!BOTH || QW == 1, "both spins: a wavefront each");
+  extern __shared__ double smem[];         // [NS][M][RS]: row m, N complex entries and a pad
+  __shared__ double a_v[NS][QRG_T][2];     // the column being orthogonalised
+  __shared__ double a_hp[NS][GR][KW][2];   // each group's partial inner products
+  __shared__ double a_h[NS][KW][2];        // h = Q_{<j}^H v
+  __shared__ double s_red[2][QW];
+  const int w = blockIdx.x;
+  const int is = BOTH ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+  const int sp = BOTH ? is : (int)blockIdx.y;
+  const int m = threadIdx.x - 64 * is, wave = m >> 6, lane = m & 63;
+  const int kk = lane % KW, grp = wave * (64 / KW) + lane / KW;
   const int RS = 2 * N + 2;  // LDS row stride (doubles)
-  double* base = phi + ((size_t)(w * 2 + sp) * M) * N * 2;
-  for (int q = threadIdx.x; q < M * N * 2; q += QRG_T) sq[(q / (2 * N)) * RS + q % (2 * N)] = base[q];
-  __syncthreads();
-  auto block_sum2 = [&](double& a, double& b) {
-    a = wave_sum(a);
-    b = wave_sum(b);
-    if (lane == 0) {
-      s_red[wave][0] = a;
-      s_red[wave][1] = b;
-    }
-    __syncthreads();
-    a = 0.0;
-    b = 0.0;
-#pragma unroll
-    for (int q = 0; q < QW; ++q) {
-      a += s_red[q][0];
-      b += s_red[q][1];
-    }
-    __syncthreads();
-  };
+  double* sq = smem + (size_t)is * M * RS;
+  double(*s_v)[2] = a_v[is];
+  double(*s_hp)[KW][2] = a_hp[is];
+  double(*s_h)[2] = a_h[is];
   double shift = 0.0;
   double* row = sq + (size_t)m * RS;
   const bool own = m < M;
-  const int r0 = 64 * wave, r1 = min(r0 + 64, M);  // this wavefront's rows
+  double* base = phi + ((size_t)(w * 2 + sp) * M) * N * 2;
+  for (int q = m; q < M * N * 2; q += QRG_T) sq[(q / (2 * N)) * RS + q % (2 * N)] = base[q];
+  __syncthreads();
   for (int j = 0; j < N; ++j) {
     cplx v = own ? cmk(row[2 * j], row[2 * j + 1]) : cmk(0.0, 0.0);
     for (int pass = 0; pass < 2 && j > 0; ++pass) {
       s_v[m][0] = v.re;
       s_v[m][1] = v.im;
       __syncthreads();
-      if (lane < j) {  // sum over this wavefront's rows of conj(q_mk) v_m, k = lane
+      if (kk < j) {  // sum over this group's rows of conj(q_mk) v_m, k = kk
         double hr[4] = {0.0, 0.0, 0.0, 0.0}, hi[4] = {0.0, 0.0, 0.0, 0.0};
-        int mm = r0;
-        for (; mm + 4 <= r1; mm += 4)
+        int mm = grp;
+        for (; mm + 3 * GR < M; mm += 4 * GR)
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            const double* q = sq + (size_t)(mm + u) * RS + 2 * lane;
-            const double vr = s_v[mm + u][0], vi = s_v[mm + u][1];
+            const double* q = sq + (size_t)(mm + u * GR) * RS + 2 * kk;
+            const double vr = s_v[mm + u * GR][0], vi = s_v[mm + u * GR][1];
             hr[u] += q[0] * vr + q[1] * vi;
             hi[u] += q[0] * vi - q[1] * vr;
           }
-        for (; mm < r1; ++mm) {
-          const double* q = sq + (size_t)mm * RS + 2 * lane;
+        for (; mm < M; mm += GR) {
+          const double* q = sq + (size_t)mm * RS + 2 * kk;
           const double vr = s_v[mm][0], vi = s_v[mm][1];
           hr[0] += q[0] * vr + q[1] * vi;
           hi[0] += q[0] * vi - q[1] * vr;
         }
-        s_hp[wave][lane][0] = (hr[0] + hr[1]) + (hr[2] + hr[3]);
-        s_hp[wave][lane][1] = (hi[0] + hi[1]) + (hi[2] + hi[3]);
+        s_hp[grp][kk][0] = (hr[0] + hr[1]) + (hr[2] + hr[3]);
+        s_hp[grp][kk][1] = (hi[0] + hi[1]) + (hi[2] + hi[3]);
       }
       __syncthreads();
       if (m < j) {
         double a = 0.0, b = 0.0;
 #pragma unroll
-        for (int q = 0; q < QW; ++q) {
-          if (64 * q < M) {
-            a += s_hp[q][m][0];
-            b += s_hp[q][m][1];
-          }
+        for (int q = 0; q < GR; ++q) {
+          a += s_hp[q][m][0];
+          b += s_hp[q][m][1];
         }
         s_h[m][0] = a;
         s_h[m][1] = b;
       }
       __syncthreads();
-      if (own)
-        for (int k = 0; k < j; ++k)
+      if (own) {
+        cplx v2 = cmk(0.0, 0.0);  // odd k, so that two chains run
+        int k = 0;
+#pragma unroll 4
+        for (; k + 1 < j; k += 2) {
           v = cfms(v, cmk(s_h[k][0], s_h[k][1]), cmk(row[2 * k], row[2 * k + 1]));
+          v2 = cfms(v2, cmk(s_h[k + 1][0], s_h[k + 1][1]), cmk(row[2 * k + 2], row[2 * k + 3]));
+        }
+        if (k < j) v = cfms(v, cmk(s_h[k][0], s_h[k][1]), cmk(row[2 * k], row[2 * k + 1]));
+        v = cadd(v, v2);
+      }
     }
-    double n2 = cabs2(v), dummy = 0.0;
-    block_sum2(n2, dummy);
+    double n2 = wave_sum_full(cabs2(v));
+    if constexpr (QW > 1) {  // two buffers, as column j + 1's sums may pass column j's readers
+      if (lane == 0) s_red[j & 1][wave] = n2;
+      __syncthreads();
+      n2 = 0.0;
+#pragma unroll
+      for (int q = 0; q < QW; ++q) n2 += s_red[j & 1][q];
+    }
     const double nrm = sqrt(n2);
     shift += log(nrm);
     if (own) {
@@ -513,8 +482,17 @@ k_qr_g(int nw, int P, int M, int N, double* __restrict__ phi, double* __restrict
     }
   }
   __syncthreads();
-  for (int q = threadIdx.x; q < M * N * 2; q += QRG_T) base[q] = sq[(q / (2 * N)) * RS + q % (2 * N)];
-  if (m == 0) logshift[(size_t)w * 2 + sp] = shift;
+  for (int q = m; q < M * N * 2; q += QRG_T) base[q] = sq[(q / (2 * N)) * RS + q % (2 * N)];
+  if constexpr (BOTH) {
+    if (logshift != nullptr) {  // the log-overlaps
+      if (lane == 0) s_red[is][0] = shift;
+      __syncthreads();
+      for (int p = threadIdx.x; p < P; p += 128)
+        logshift[((size_t)w * P + p) * 2] -= s_red[0][0] + s_red[1][0];
+    }
+  } else {
+    if (m == 0) logshift[(size_t)w * 2 + sp] = shift;
+  }
 }
 
 __global__ void k_apply_shift(int nw, int P, const double* __restrict__ logshift,
@@ -529,24 +507,41 @@ __global__ void k_apply_shift(int nw, int P, const double* __restrict__ logshift
 
 namespace {
 
-template <int QW>
-hipError_t launch_qr_gw(const afqmc_ctx_s* c, int nw, double* phi, double* shift) {
-  const size_t lds = (size_t)c->M * (2 * c->N + 2) * sizeof(double);
-  auto kern = k_qr_g<QW>;
+template <int QW, int KW, bool BOTH = false>
+hipError_t launch_qr_w(const afqmc_ctx_s* c, int nw, double* phi, double* shift) {
+  const size_t lds = (size_t)(BOTH ? 2 : 1) * c->M * (2 * c->N + 2) * sizeof(double);
+  auto kern = k_qr_g<QW, KW, BOTH>;
   hipError_t e =
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(nw, 2), dim3(64 * QW), lds, c->stream, nw, c->P, c->M, c->N, phi,
-                     shift);
+  hipLaunchKernelGGL(kern, dim3(nw, BOTH ? 1 : 2), dim3(BOTH ? 128 : 64 * QW), lds, c->stream, nw, c->P, c->M,
+                     c->N, phi, shift);
   return hipGetLastError();
 }
 
 }  // namespace
 
+hipError_t launch_qr(const afqmc_ctx_s* c, int nw, double* phi, double* logov) {
+  if (nw <= 0) return hipSuccess;
+  if (c->M > 64 || c->N > 16) return hipErrorInvalidValue;
+  return launch_qr_w<1, 16, true>(c, nw, phi, logov);
+}
+
 hipError_t launch_qr_g(const afqmc_ctx_s* c, int nw, double* phi, double* logov, double* shift) {
   if (nw <= 0) return hipSuccess;
   if (c->M > 192) return hipErrorInvalidValue;
-  hipError_t e = c->M <= 128 ? launch_qr_gw<2>(c, nw, phi, shift) : launch_qr_gw<3>(c, nw, phi, shift);
+  // wavefronts: as many more than the rows need (64 each) as keep a CU busy with the
+  // workgroups that its LDS takes (M = 128, N = 32: 68 KB)
+  const int M = c->M, N = c->N;
+  hipError_t e;
+  if (N <= 16)
+    e = M <= 128 ? launch_qr_w<2, 16>(c, nw, phi, shift) : launch_qr_w<4, 16>(c, nw, phi, shift);
+  else if (N <= 32)
+    e = M <= 80    ? launch_qr_w<2, 32>(c, nw, phi, shift)
+        : M <= 128 ? launch_qr_w<4, 32>(c, nw, phi, shift)
+                   : launch_qr_w<8, 32>(c, nw, phi, shift);
+  else
+    e = launch_qr_w<8, 64>(c, nw, phi, shift);
   if (e != hipSuccess) return e;
   if (logov != nullptr) {
     const int n = nw * c->P;
