@@ -857,6 +857,10 @@ afqmc_status afqmc_metropolis_x(afqmc_ctx c, int32_t nw, const void* phi, double
   }
   const int nflip = (c->hidden_kind == AFQMC_HIDDEN_ISING) ? c->K : 1;
   for (int s = 0; s < n_sweep; ++s) {
+    if (ising_sweep_takes(c)) {
+      HIPCALL(c, launch_ising_sweep(c, nw, ph, y, phiT, lo, nacc, seed, step, s), "Ising sweep");
+      continue;
+    }
     for (int f = 0; f < nflip; ++f) {
       const int flip_k = (c->hidden_kind == AFQMC_HIDDEN_ISING) ? f : -1;
       HIPCALL(c, launch_proposal(c, nw, y, ytry, seed, step, s, flip_k, c->proposal), "proposal");

@@ -175,6 +175,10 @@ hipError_t launch_phi_narrow(const afqmc_ctx_s* c, size_t n, const double* src, 
 hipError_t launch_trial_build_g(const afqmc_ctx_s* c, int n_samples, const double* y,
                                 double* phiT, double* ubuf, void* scratch = nullptr,
                                 size_t scratch_bytes = 0);
+bool ising_sweep_takes(const afqmc_ctx_s* c);
+hipError_t launch_ising_sweep(const afqmc_ctx_s* c, int nw, const double* phi, double* y,
+                              double* phiT, double* logov, int* nacc, uint64_t seed, uint64_t step,
+                              int sweep);
 hipError_t launch_overlap_lu(const afqmc_ctx_s* c, int nw, const double* phi, const double* phiT,
                              double* logov, double* theta);
 hipError_t launch_overlap_g(const afqmc_ctx_s* c, int nw, const double* phi, const double* phiT,

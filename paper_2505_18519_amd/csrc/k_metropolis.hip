@@ -3,7 +3,8 @@
 // AFQMC_Metro_constraint_cos; App. B steps 2 and 3).
 //
 // One proposal round = k_proposal (y' for every path) -> trial build ->
-// overlap (det only) at the moved walker -> k_accept.  The paths sample
+// overlap (det only) at the moved walker -> k_accept (Ising flips of small systems with
+// diagonal generators: all rounds of a sweep in k_ising_sweep, with the overlap).  The paths sample
 // P(y; phi) ~ p_T(y) |O(y; phi)|: prior proposals (App. B) are accepted with
 // |O(y')| / |O(y)|, the Gaussian random walk with |O(y')| N(y') / (|O(y)| N(y)),
 // Ising single-spin flips with |O(y')| / |O(y)|, the learned proposal with
