@@ -275,7 +275,7 @@ def learned_study(args):
                    "L_scale": L_SCALE, **STABLE},
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_FP32_MFMA,
                      "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_MFMA, "traffic": None,
-                     "kernel": "k_contract_sh, FP32 products (+ k_combine) in afqmc_local_energy",
+                     "kernel": "k_contract_f32, FP32 products (+ k_combine) in afqmc_local_energy",
                      "ms_per_launch": L["contraction_ms"], "flops_per_launch": flops},
         "learned_mixed": L,
         "random_walk_fp64": R,
@@ -752,7 +752,8 @@ def main():
                      "traffic": measured_traffic(args.workload),
                      "kernel": ("k_contract" if sys_.M <= 64 and sys_.N <= 16 and precision == 0
                                 and not ctx.ctrial else
-                                "k_contract_sh" if precision in (1, 2, 3) and not ctx.ctrial
+                                "k_contract_f32" if precision == 1 and not ctx.ctrial else
+                                "k_contract_sh" if precision in (2, 3)
                                 else "k_contract_q")
                                + (" (complex trial)" if ctx.ctrial else "")
                                + " (+ k_combine) in afqmc_local_energy",
