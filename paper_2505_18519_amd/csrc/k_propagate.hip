@@ -719,8 +719,10 @@ hipError_t launch_weight(const afqmc_ctx_s* c, int nw, const double* xi, const d
 // registers (V_re and -V_im), the real one-body factors' operands read from L2
 // at their uses, the iterate in one LDS tile with two barriers per Horner
 // step, and X (the start of the Horner recursion) in a second LDS tile, or in
-// registers (each wavefront its own rows) when two tiles exceed the LDS.  The
-// imaginary part is accumulated as V_re Y_im - (-V_im) Y_re.
+// registers (each wavefront its own rows) when two tiles exceed the LDS.  In FP64
+// every product and sum comes in the order of k_taylor_q, so that the bits do not
+// depend on which of the two a call's walker count selects; in FP32 the imaginary part
+// is accumulated as V_re Y_im - (-V_im) Y_re.
 // Computes dst = El T_n(V) Er src per block (Er may be null: identity).  The
 // walker step has El = Er = e^{-tau h1/2}, src = dst, two spins; a trial slice
 // has one M x N block per path and src either the previous slice or, for the
@@ -826,8 +828,9 @@ k_taylor_g(int n, int M, int N, int MT, int n_taylor, int spins, const double* _
     for (int q = threadIdx.x; q < 2 * MT * NT; q += blockDim.x) sX[q] = sY[q];
     __syncthreads();
   }
+  constexpr bool F64 = sizeof(T) == 8;
   for (int j = n_taylor; j >= 1; --j) {
-    acc_t are[NTC], aim1[NTC], aim2[NTC];
+    acc_t are[NTC], aim1[NTC], aim2[NTC];  // FP64: the imaginary part in aim1 alone
 #pragma unroll
     for (int ct = 0; ct < NTC; ++ct) are[ct] = aim1[ct] = aim2[ct] = mm::zero();
 #pragma unroll
@@ -840,9 +843,15 @@ k_taylor_g(int n, int M, int N, int MT, int n_taylor, int spins, const double* _
             const T* yb = sY + ((16 * t + mm::row(g, r)) * NT + 16 * ct + c) * 2;
             const T yr = yb[0], yi = yb[1];
             are[ct] = mm::fma(vr[t][r], yr, are[ct]);
-            are[ct] = mm::fma(nvi[t][r], yi, are[ct]);
-            aim1[ct] = mm::fma(vr[t][r], yi, aim1[ct]);
-            aim2[ct] = mm::fma(nvi[t][r], yr, aim2[ct]);
+            if constexpr (F64) {
+              aim1[ct] = mm::fma(vr[t][r], yi, aim1[ct]);
+              are[ct] = mm::fma(nvi[t][r], yi, are[ct]);
+              aim1[ct] = mm::fma(nvi[t][r], -yr, aim1[ct]);
+            } else {
+              are[ct] = mm::fma(nvi[t][r], yi, are[ct]);
+              aim1[ct] = mm::fma(vr[t][r], yi, aim1[ct]);
+              aim2[ct] = mm::fma(nvi[t][r], yr, aim2[ct]);
+            }
           }
     const T invj = (T)(1.0 / (double)j);
     acc_t y[NTC][2];
@@ -859,8 +868,13 @@ k_taylor_g(int n, int M, int N, int MT, int n_taylor, int spins, const double* _
           xr_ = xv[0];
           xi_ = xv[1];
         }
-        y[ct][0][r] = xr_ + are[ct][r] * invj;
-        y[ct][1][r] = xi_ + (aim1[ct][r] - aim2[ct][r]) * invj;
+        if constexpr (F64) {
+          y[ct][0][r] = fma(are[ct][r], invj, xr_);
+          y[ct][1][r] = fma(aim1[ct][r], invj, xi_);
+        } else {
+          y[ct][0][r] = xr_ + are[ct][r] * invj;
+          y[ct][1][r] = xi_ + (aim1[ct][r] - aim2[ct][r]) * invj;
+        }
       }
     __syncthreads();
     store(sY, y);

@@ -177,7 +177,8 @@ hipError_t launch_q(const afqmc_ctx_s* c, int n, int spins, int n_taylor, const 
 // fewer on (N = 24, M = 96: 1.33, move 1043 -> 945 us; N = 25, M = 100: 1.28, 654 -> 633),
 // not at equal counts (N = 32, M = 128: 1512 -> 1572; N = 16, M = 64 slices 920 -> 1160), and
 // not where a V gives too few wavefronts to cover the chip (M = 128, N = 8, 30 walkers: 207
-// -> 337 us: there a block's row tiles are the parallel part).
+// -> 337 us: there a block's row tiles are the parallel part).  Both give the same bits, so
+// that a walker does not depend on how many others share the call.
 bool taylor_q_better(const afqmc_ctx_s* c, int n, int spins) {
   const long nct = (spins * c->N + 7) / 8, ntc = (c->N + 15) / 16;
   const long here = nct * 2 * (4 * ((c->M + 3) / 4)), there = (long)spins * ntc * 4 * c->MT;
