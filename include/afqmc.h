@@ -29,8 +29,10 @@
  * device copy of the system made by afqmc_create.  Calls are asynchronous on
  * the context's stream; they validate arguments on the host and never abort.
  * Non-finite results are data, flagged per walker (see "Numerical events").
- * Walker k's random numbers depend only on (seed, step, k), so any nw-prefix
- * of a batch reproduces the same walkers.
+ * Walker k's random numbers depend only on (seed, step, k), and its kernels and
+ * orders of sums not on nw, so any nw-prefix of a batch reproduces the same walkers,
+ * bit for bit, until a call that acts on the whole population (population control,
+ * training of the proposal network).
  */
 #ifndef AFQMC_H
 #define AFQMC_H

@@ -10,14 +10,14 @@
 #include <vector>
 
 #include "afqmc_internal.h"
+#include "contract_sum.h"
 
 // Fixed per-GPU scratch of the entry point that allocates nothing
 // (afqmc_local_energy_static).  In host code this name is only a stand-in for
 // the symbol: every host use goes through the device address that
 // hipGetSymbolAddress returns for the current device (scratch_address).
-// Past the documented size it holds the contraction's partial sums: at least 16
-// vectors go to each of their ranges (two ranges from 28 vectors on), so 16 bytes
-// per path and range is below 1/12 of the vb array.
+// Past the documented size it has room for the contraction's block sums; a call
+// whose block sums need more runs unsplit, with the same results.
 constexpr size_t kPartialBytes = AFQMC_STATIC_SCRATCH_BYTES / 12;
 static __device__ __align__(256) unsigned char scratch[AFQMC_STATIC_SCRATCH_BYTES + kPartialBytes];
 
@@ -619,36 +619,32 @@ afqmc_status afqmc_green(afqmc_ctx c, int32_t nw, const void* phi, const double*
 }
 
 // The contraction kernel of the context's family and precision into per-path
-// vb and ep, then the walker-level combination.  part: room for partial sums of
-// E_p, 16 bytes for each path and range of contract_q_splits.
+// vb and ep, then the walker-level combination.  part: part_bytes of room for the
+// block sums of E_p of calls that split the vectors over workgroups.
 static hipError_t contraction_kernels(afqmc_ctx c, int32_t nw, const double* phiT,
                                       const void* theta, const void* logov, void* xbar, double* vb,
-                                      void* eloc, double* ep, double* part, int* flags) {
+                                      void* eloc, double* ep, double* part, size_t part_bytes,
+                                      int* flags) {
   const double* th = static_cast<const double*>(theta);
   const double* lo = static_cast<const double*>(logov);
   hipError_t e;
-  const double* epart = ep;
-  int nsplit = 1;
-  if (c->precision == AFQMC_PREC_FP32 && !c->ctrial) {
-    nsplit = contract_f32_splits(c, nw);
-    if (nsplit > 1) epart = part;
-    e = launch_contract_f32(c, nw, nsplit, phiT, th, lo, vb, nsplit > 1 ? part : ep);
-  } else if (c->precision != AFQMC_PREC_FP64 && !c->ctrial) {
-    nsplit = contract_sh_splits(c, nw);
-    if (nsplit > 1) epart = part;
-    e = launch_contract_sh(c, nw, nsplit, phiT, th, lo, vb, nsplit > 1 ? part : ep);
-  } else if (c->precision != AFQMC_PREC_FP64) {
+  contract_plan p;
+  auto run = [&](auto launch, contract_plan plan) {
+    if (plan.nsplit > 1 && plan.part_bytes((size_t)nw * c->P) <= part_bytes) p = plan;
+    return launch(c, nw, p.nsplit, phiT, th, lo, vb, p.nsplit > 1 ? part : ep);
+  };
+  if (c->precision == AFQMC_PREC_FP64)
+    e = contract_in_registers(c) ? run(launch_contract, contract_r_plan(c, nw))
+                                 : run(launch_contract_q, contract_q_plan(c, nw));
+  else if (c->ctrial)
     e = launch_contract_g(c, nw, phiT, th, lo, vb, ep);
-  } else if (contract_in_registers(c, nw)) {
-    e = launch_contract(c, nw, phiT, th, lo, vb, ep);
-  } else {
-    nsplit = contract_q_splits(c, nw);
-    if (nsplit > 1) epart = part;
-    e = launch_contract_q(c, nw, nsplit, phiT, th, lo, vb, nsplit > 1 ? part : ep);
-  }
+  else if (c->precision == AFQMC_PREC_FP32)
+    e = run(launch_contract_f32, contract_f32_plan(c, nw));
+  else
+    e = run(launch_contract_sh, contract_sh_plan(c, nw));
   if (e != hipSuccess) return e;
-  return launch_combine(c, nw, vb, epart, nsplit, ep, lo, static_cast<double*>(xbar),
-                        static_cast<double*>(eloc), flags);
+  return launch_combine(c, nw, vb, part, p.nsplit > 1 ? p.blocks : 0, p.waves, ep, lo,
+                        static_cast<double*>(xbar), static_cast<double*>(eloc), flags);
 }
 
 static afqmc_status contraction(afqmc_ctx c, int32_t nw, const double* phiT, const void* theta,
@@ -662,9 +658,9 @@ static afqmc_status contraction(afqmc_ctx c, int32_t nw, const double* phiT, con
   hipError_t fe;
   int* flags = flag_words(c, nw, &fe);
   HIPCALL(c, fe, "flags");
-  // the V buffer, idle outside the move, takes the partial sums
+  // the V and U buffers, idle outside the move and the trial builds, take the block sums
   HIPCALL(c, contraction_kernels(c, nw, phiT, theta, logov, xbar, vb, eloc, ep,
-                                 ws_ptr<double>(c, L.vmat), flags),
+                                 ws_ptr<double>(c, L.vmat), L.qrshift - L.vmat, flags),
           "contraction");
   return numeric_check_end(c, nw, flags);
 }
@@ -718,7 +714,7 @@ afqmc_status afqmc_local_energy_static(afqmc_ctx c, int32_t nw, const double* ph
   double* ep = e_sample ? static_cast<double*>(e_sample) : reinterpret_cast<double*>(base + vb_bytes);
   HIPCALL(c, contraction_kernels(c, nw, phiT, theta, logov, xbar, vb, eloc, ep,
                                  reinterpret_cast<double*>(base + AFQMC_STATIC_SCRATCH_BYTES),
-                                 nullptr),
+                                 kPartialBytes, nullptr),
           "static contraction");
   return AFQMC_OK;
 }

@@ -121,14 +121,20 @@ hipError_t launch_trial_build(const afqmc_ctx_s* c, int n_samples, const double*
                               double* ubuf);
 hipError_t launch_overlap(const afqmc_ctx_s* c, int nw, const double* phi, const double* phiT,
                           double* logov, double* theta, double* gdiag);
-hipError_t launch_contract(const afqmc_ctx_s* c, int nw, const double* phiT, const double* theta,
-                           const double* logov, double* vb, double* ep);
+// Contractions: per-path vb and E_p, the vectors in nsplit ranges (contract_sum.h; the plan of
+// the same kernel): ep [nw P], or with nsplit > 1 the block sums that launch_combine adds
+struct contract_plan;
+// FP64, one wavefront per path (small systems with N > 12)
+bool contract_in_registers(const afqmc_ctx_s* c);
+contract_plan contract_r_plan(const afqmc_ctx_s* c, int nw);
+hipError_t launch_contract(const afqmc_ctx_s* c, int nw, int nsplit, const double* phiT,
+                           const double* theta, const double* logov, double* vb, double* ep);
 // flags (may be null): per-walker AFQMC_NUMERIC_* bits OR-ed in where a
 // kernel finds a non-finite result
-// ep [nw][P] is the sum of epart's nsplit parts, written here when nsplit > 1
+// nblk > 0: ep [nw][P] is the sum of epart's blocks, written here
 hipError_t launch_combine(const afqmc_ctx_s* c, int nw, const double* vb, const double* epart,
-                          int nsplit, double* ep, const double* logov, double* xbar, double* eloc,
-                          int* flags);
+                          int nblk, int nwv, double* ep, const double* logov, double* xbar,
+                          double* eloc, int* flags);
 // scratch (may be null): device memory free for the call, used by BF16 contexts
 // for their split coefficients when it holds scratch_bytes >= 8 nw GP
 hipError_t launch_vbuild(const afqmc_ctx_s* c, int nw, const double* xi, const double* xbar,
@@ -185,11 +191,8 @@ hipError_t launch_overlap_g(const afqmc_ctx_s* c, int nw, const double* phi, con
                             double* logov, double* theta, double* gdiag);
 hipError_t launch_contract_g(const afqmc_ctx_s* c, int nw, const double* phiT, const double* theta,
                              const double* logov, double* vb, double* ep);
-// whether the FP64 contraction of nw walkers runs one wavefront per path (launch_contract)
-bool contract_in_registers(const afqmc_ctx_s* c, int nw);
-// FP64 contraction of real trials at any size (k_contract_q.hip), over nsplit ranges of the
-// vectors: epart [nsplit][nw P] complex, the ranges' parts of E_p
-int contract_q_splits(const afqmc_ctx_s* c, int nw);
+// FP64 contraction, real and complex trials, at any size (k_contract_q.hip)
+contract_plan contract_q_plan(const afqmc_ctx_s* c, int nw);
 hipError_t launch_contract_q(const afqmc_ctx_s* c, int nw, int nsplit, const double* phiT,
                              const double* theta, const double* logov, double* vb, double* epart);
 hipError_t launch_taylor_g(const afqmc_ctx_s* c, int nw, const double* vmat, double* phi);
@@ -239,13 +242,13 @@ hipError_t launch_trial_slices(const afqmc_ctx_s* c, int n, const double* y, dou
                                double* vbuf);
 hipError_t launch_qr_g(const afqmc_ctx_s* c, int nw, double* phi, double* logov, double* shift);
 hipError_t launch_to_float(const afqmc_ctx_s* c, size_t n, const double* src, float* dst);
-// FP32 contraction (real trial), over ranges of the vectors as contract_q_splits
-int contract_f32_splits(const afqmc_ctx_s* c, int nw);
+// FP32 contraction (real trial)
+contract_plan contract_f32_plan(const afqmc_ctx_s* c, int nw);
 hipError_t launch_contract_f32(const afqmc_ctx_s* c, int nw, int nsplit, const double* phiT,
                                const double* theta, const double* logov, double* vb,
                                double* epart);
-// split-BF16 and BF16 contractions, likewise
-int contract_sh_splits(const afqmc_ctx_s* c, int nw);
+// split-BF16 and BF16 contractions
+contract_plan contract_sh_plan(const afqmc_ctx_s* c, int nw);
 hipError_t launch_contract_sh(const afqmc_ctx_s* c, int nw, int nsplit, const double* phiT,
                               const double* theta, const double* logov, double* vb,
                               double* epart);

@@ -211,7 +211,22 @@ __device__ __forceinline__ double wave_max_full(double v) {
               fmax(readlane_f64(v, 32), readlane_f64(v, 48)));
 }
 
-// the same for a float
+// sum over each 16-lane row, on every lane of the row
+__device__ __forceinline__ double row_sum(double x) {
+  x += dpp_f64<0xB1>(x);
+  x += dpp_f64<0x4E>(x);
+  x += dpp_f64<0x141>(x);
+  return x + dpp_f64<0x140>(x);
+}
+
+// sum over the wavefront, all 64 lanes active: DPP moves within each 16-lane row, then the
+// rows' sums by readlane
+__device__ __forceinline__ double wave_sum_full(double v) {
+  v = row_sum(v);
+  return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
+}
+
+// wave_max_full for a float
 __device__ __forceinline__ float wave_max_full_f32(float v) {
   v = fmaxf(v, __int_as_float(dpp_i32<0xB1>(__float_as_int(v))));
   v = fmaxf(v, __int_as_float(dpp_i32<0x4E>(__float_as_int(v))));

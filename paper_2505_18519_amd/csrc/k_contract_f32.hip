@@ -36,17 +36,12 @@
 // paths 33.3 -> 33.5.  With few paths the vectors are split over workgroups: M = 70,
 // N = 22, 240 vectors, 40 paths 1.79 -> 0.13 ms.
 #include "afqmc_internal.h"
+#include "contract_sum.h"
 #include "dev_common.h"
 
 namespace {
 
-// sum over each 16-lane row, on every lane of the row
-__device__ __forceinline__ double row_sum(double x) {
-  x += dpp_f64<0xB1>(x);
-  x += dpp_f64<0x4E>(x);
-  x += dpp_f64<0x141>(x);
-  return x + dpp_f64<0x140>(x);
-}
+constexpr int GRP = 2;  // groups of vectors in a granule of the sum over them
 
 template <int KT, int T>
 struct Shape {
@@ -109,8 +104,8 @@ k_contract_f32(int n_samples, int M, int N, int G, const fx4* Lop,
   }
   // G vectors and h1' in groups of two; this workgroup's range of them
   const int ngrp = (G + 2) / 2;
-  const int grp0 = (int)blockIdx.y * ngrp / (int)gridDim.y;
-  const int grp1 = ((int)blockIdx.y + 1) * ngrp / (int)gridDim.y;
+  block_range rng((ngrp + GRP - 1) / GRP, blockIdx.y, gridDim.y);
+  const int grp0 = rng.begin() * GRP, grp1 = min(rng.b.begin(rng.last) * GRP, ngrp);
   // operands of one row tile, read ahead: a[t] is reloaded right after its products
   fx4 a[KT];
   const fx4* Lw = Lop + (size_t)min(2 * grp0 + v1, G) * SLAB;
@@ -126,7 +121,7 @@ k_contract_f32(int n_samples, int M, int N, int G, const fx4* Lop,
     yr[it] = sY + ((R / S) * 4 * KT + g) * 16 * T + pp * S + R % S;
   }
   const bool late = Sh::NPR == 1 && pp == 1;  // (uniform in the wavefront)
-  double e_re = 0.0, e_im = 0.0;  // this lane's share of E_p
+  double e_re = 0.0, e_im = 0.0;  // this lane's share of E_p in the block of vectors
   if (Sh::NPR == 2 && pair == 1) __syncthreads();  // one barrier behind the first pair
   fx4 f[T][2];
   auto stage1 = [&](int grp) {
@@ -226,6 +221,7 @@ k_contract_f32(int n_samples, int M, int N, int G, const fx4* Lop,
     }
   };
   stage1(grp0);
+  int bend = rng.end() * GRP;
   for (int grp = grp0; grp < grp1; ++grp) {
     __syncthreads();
 #pragma unroll
@@ -258,19 +254,23 @@ k_contract_f32(int n_samples, int M, int N, int G, const fx4* Lop,
     if (!late) trace(grp);
     if (grp + 1 < grp1) stage1(grp + 1);
     if (late) trace(grp);
+    if (grp + 1 == bend || grp + 1 == ngrp) {
+      rng.add(e_re, e_im, epart, w1, T, n_samples, s, valid, active);
+      e_re = e_im = 0.0;
+      bend = rng.end() * GRP;
+    }
   }
   if (Sh::NPR == 2 && pair == 0) __syncthreads();
-  e_re = wave_sum(e_re);
-  e_im = wave_sum(e_im);
-  if (lane == 0) *reinterpret_cast<double2*>(sT + wave * 2) = make_double2(e_re, e_im);
+  const double2 e_wave = rng.total();  // with all lanes active
+  if (lane == 0) *reinterpret_cast<double2*>(sT + wave * 2) = e_wave;
   __syncthreads();
-  if (valid && w1 == 0 && lane == 0) {
+  if (!rng.split && valid && w1 == 0 && lane == 0) {
     double re = 0.0, im = 0.0;
     for (int w = 0; w < T; ++w) {
       re += sT[(wave + w) * 2];
       im += sT[(wave + w) * 2 + 1];
     }
-    *reinterpret_cast<double2*>(epart + ((size_t)blockIdx.y * n_samples + s) * 2) =
+    *reinterpret_cast<double2*>(epart + (size_t)s * 2) =
         active ? make_double2(re, im) : make_double2(0.0, 0.0);
   }
 }
@@ -305,26 +305,13 @@ __global__ void k_to_f32_op(size_t n, int MT, const double* __restrict__ src,
 
 }  // namespace
 
-// Ranges of g: the fewest that fill the rounds of workgroups the chip takes at once (256, or
-// three a CU with the small ones of N <= 8) to within 4 %, at least eight groups of vectors to
-// a range.  256 paths of M = 96, N = 24 (64 workgroups): 2.8 ms in one range, 0.81 in six.
-// k P <= M^2 keeps the partial sums (16 bytes a path and range) within the workspace's V
-// buffer, which holds them.
-int contract_f32_splits(const afqmc_ctx_s* c, int nw) {
+// Ranges of g (slots: one workgroup a CU, or three of the small ones of N <= 8; at least
+// eight groups of vectors to a range).  256 paths of M = 96, N = 24 (64 workgroups): 2.8 ms in
+// one range, 0.81 in six.
+contract_plan contract_f32_plan(const afqmc_ctx_s* c, int nw) {
   const int pp = c->N > 24 ? 2 : 4;
-  const long units = ((long)nw * c->P + pp - 1) / pp, slots = c->N > 8 ? 256 : 768;
-  const int ngrp = (c->G + 2) / 2;
-  int best = 1;
-  double fill = 0.0;
-  for (int k = 1; k <= 16 && k * 8 <= ngrp && k * c->P <= c->M * c->M; ++k) {
-    const long u = units * k;
-    const double x = (double)u / (double)((u + slots - 1) / slots * slots);
-    if (x > fill + 0.04) {
-      best = k;
-      fill = x;
-    }
-  }
-  return best;
+  return plan_splits(((long)nw * c->P + pp - 1) / pp, c->N > 8 ? 256 : 768,
+                     ((c->G + 2) / 2 + GRP - 1) / GRP, 8 / GRP, (c->N + 7) / 8);
 }
 
 hipError_t launch_contract_f32(const afqmc_ctx_s* c, int nw, int nsplit, const double* phiT,

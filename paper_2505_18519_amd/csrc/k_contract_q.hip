@@ -22,7 +22,7 @@
 // (i Theta), the second from Theta's parts exchanged and signed.
 // PP = 2 paths share a workgroup where L_g's L2 traffic would bound (N <= 20): each L
 // operand then feeds both paths.  A few paths (or a last round of workgroups that fills
-// little of the chip) are split further over ranges of g (contract_q_splits).
+// little of the chip) are split further over ranges of g (contract_q_plan).
 //
 // Measured on 2048 (or as many as fill the chip) paths, before (operands in registers,
 // or for N > 32 streamed, N padded to 16) and now, TFLOP/s of the unpadded products:
@@ -30,6 +30,7 @@
 // 128, 16: 42 -> 56; 112, 28: 45 -> 59; 142, 35: 18 -> 54; 160, 40: 31 -> 58; 128, 32:
 // 60 -> 60.
 #include "afqmc_internal.h"
+#include "contract_sum.h"
 #include "dev_common.h"
 
 namespace {
@@ -90,12 +91,14 @@ k_contract_q(int n_samples, int M, int N, int G, int KT, const double* __restric
   double* sE = sD + 2 * NW * 32;          // [NW][2]
 
   const int s0 = blockIdx.x * PP;
-  double* ep = epart + (size_t)blockIdx.y * n_samples * 2;  // this range's part of E_p
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int g = lane >> 4, c = lane & 15;
   // path of this wavefront in stage 2 and its place among that path's wavefronts
   const int pw = wave / NWP, wi = wave % NWP;
+  // groups of this workgroup's range; vectors 0 .. G (h1') in all
+  block_range rng((G + GV) / GV, blockIdx.y, gridDim.y);
+  const int grp0 = rng.begin(), grp1 = rng.b.begin(rng.last);
   bool active[PP];  // singular paths contribute zero
   bool any = false;
 #pragma unroll
@@ -105,7 +108,11 @@ k_contract_q(int n_samples, int M, int N, int G, int KT, const double* __restric
     if (s0 + p < n_samples && !active[p]) {
       for (int q = tid + 64 * NW * blockIdx.y; q < 2 * G; q += 64 * NW * gridDim.y)
         vb[(size_t)(s0 + p) * G * 2 + q] = 0.0;
-      if (tid < 2) ep[2 * (size_t)(s0 + p) + tid] = 0.0;
+      if (rng.split) {
+        if (wave < NWP) zero_blocks(rng, epart, wave, NWP, n_samples, s0 + p, lane);
+      } else if (tid < 2) {
+        epart[2 * (size_t)(s0 + p) + tid] = 0.0;
+      }
     }
   }
   if (!any) return;
@@ -125,15 +132,11 @@ k_contract_q(int n_samples, int M, int N, int G, int KT, const double* __restric
   }
   const int v = wave & 3, h = wave >> 2;
   const size_t slab = (size_t)MT * MT;
-  // groups of this workgroup's range; vectors 0 .. G (h1') in all
-  const int ngrp = (G + GV) / GV;
-  const int grp0 = (int)blockIdx.y * ngrp / (int)gridDim.y;
-  const int grp1 = ((int)blockIdx.y + 1) * ngrp / (int)gridDim.y;
   // the last 16-wide tile of the contraction index holds more than 8 of the M rows
   const bool whole = M > 16 * KT - 8;
   const int KH = (M + 7) / 8;
 
-  double ex_re = 0.0, ex_im = 0.0, vb2_re = 0.0, vb2_im = 0.0, e1_re = 0.0, e1_im = 0.0;
+  double e_re = 0.0, e_im = 0.0;  // this lane's share of E_p in the block of vectors
 
   const unsigned lofs = g * MT + c;  // this lane's entry of a 4 x 16 operand of L
   auto load_l = [&](const double* Lg, int tb, int t, double (&o)[4][KC]) {
@@ -375,8 +378,8 @@ k_contract_q(int n_samples, int M, int N, int G, int KT, const double* __restric
       }
     });
     const double t_re = fma(2.0, o_re, d_re), t_im = fma(2.0, o_im, d_im);
-    ex_re += ok_v ? t_re : 0.0;
-    ex_im += ok_v ? t_im : 0.0;
+    e_re -= ok_v ? 0.5 * t_re : 0.0;
+    e_im -= ok_v ? 0.5 * t_im : 0.0;
   };
   // the diagonal elements f_v[i][i] of both spins, summed over this wavefront's tiles
   auto put_d = [&](double* d) {
@@ -394,6 +397,7 @@ k_contract_q(int n_samples, int M, int N, int G, int KT, const double* __restric
   const double* Lv = Lpad + (size_t)min(GV * grp0 + v, G) * slab;  // this wavefront's vector
   load_l(Lv, h * KC, 0, ac);
   __syncthreads();
+  int bend = rng.end();
   for (int grp = grp0; grp < grp1; ++grp) {
     const double* Lnext = Lpad + (size_t)min(GV * (grp + 1) + v, G) * slab;
     unrolled<NC * NG>(
@@ -476,33 +480,31 @@ k_contract_q(int n_samples, int M, int N, int G, int KT, const double* __restric
       if (lane < 16 && (c & 3) == 0 && active[PP > 1 ? pw : 0]) {
         if (vec < G) {
           *reinterpret_cast<double2*>(vb + ((size_t)(s0 + pw) * G + vec) * 2) = make_double2(x, z);
-          vb2_re += x * x - z * z;
-          vb2_im += 2.0 * x * z;
+          e_re += 0.5 * (x * x - z * z);
+          e_im += x * z;
         } else if (vec == G) {
-          e1_re = x;
-          e1_im = z;
+          e_re += x;
+          e_im += z;
         }
       }
     }
-  }
-  ex_re = wave_sum(ex_re);
-  ex_im = wave_sum(ex_im);
-  if (lane == 0) {
-    sE[wave * 2] = ex_re;
-    sE[wave * 2 + 1] = ex_im;
-  }
-  __syncthreads();
-  if (wi == 0 && active[PP > 1 ? pw : 0]) {
-    const double b_re = wave_sum(e1_re + 0.5 * vb2_re), b_im = wave_sum(e1_im + 0.5 * vb2_im);
-    if (lane == 0) {
-      double xr = 0.0, xi = 0.0;
-      for (int q = 0; q < NWP; ++q) {
-        xr += sE[(wave + q) * 2];
-        xi += sE[(wave + q) * 2 + 1];
-      }
-      ep[2 * (size_t)(s0 + pw)] = b_re - 0.5 * xr;
-      ep[2 * (size_t)(s0 + pw) + 1] = b_im - 0.5 * xi;
+    if (grp + 1 == bend) {
+      rng.add(e_re, e_im, epart, wi, NWP, n_samples, s0 + pw, active[PP > 1 ? pw : 0], true);
+      e_re = e_im = 0.0;
+      bend = rng.end();
     }
+  }
+  const double2 e_wave = rng.total();  // with all lanes active
+  if (lane == 0) *reinterpret_cast<double2*>(sE + wave * 2) = e_wave;
+  __syncthreads();
+  if (!rng.split && wi == 0 && lane == 0 && active[PP > 1 ? pw : 0]) {
+    double xr = 0.0, xi = 0.0;
+    for (int q = 0; q < NWP; ++q) {
+      xr += sE[(wave + q) * 2];
+      xi += sE[(wave + q) * 2 + 1];
+    }
+    epart[2 * (size_t)(s0 + pw)] = xr;
+    epart[2 * (size_t)(s0 + pw) + 1] = xi;
   }
 }
 
@@ -528,28 +530,16 @@ hipError_t launch_q(const afqmc_ctx_s* c, int n, int nsplit, const double* phiT,
 // N = 20: 16.0 and 16.4.
 static int paths_per_group(int NG, int KT) { return NG <= 4 || (NG == 5 && KT <= 7) ? 2 : 1; }
 
-// Ranges of g that the paths' workgroups are split into: the fewest that fill the rounds
-// of workgroups (slots = what the CUs hold at once: by registers 4 a CU up to N = 12, 2 up
-// to N = 28, 1 of eight wavefronts past that) to within 4 % of the best, with at least
-// four groups of vectors to a range.  600 paths of M = 142, N = 35 fill 2.3 rounds of 256:
-// 24.7 ms in one range, 17.9 in three.  k P <= M^2 keeps the partial sums (16 bytes a
-// path and range) within the workspace's V buffer, which holds them.
-int contract_q_splits(const afqmc_ctx_s* c, int nw) {
+// Ranges of g that the paths' workgroups are split into (slots: what the CUs hold at once, by
+// registers 4 a CU up to N = 12, 2 up to N = 28, 1 of eight wavefronts past that; at least
+// four groups of vectors to a range).  600 paths of M = 142, N = 35 fill 2.3 rounds of 256:
+// 24.7 ms in one range, 17.9 in several.
+contract_plan contract_q_plan(const afqmc_ctx_s* c, int nw) {
   const int NG = (c->N + 3) / 4, pp = c->ctrial ? 1 : paths_per_group(NG, c->MT / 16);
-  const long units = ((long)nw * c->P + pp - 1) / pp;
-  const long slots = NG <= 3 ? 1024 : NG <= 7 ? 512 : 256;
-  const int ngrp = (c->G + GV) / GV;
-  int best = 1;
-  double fill = 0.0;
-  for (int k = 1; k <= 16 && k * 4 <= ngrp && k * c->P <= c->M * c->M; ++k) {
-    const long u = units * k;
-    const double x = (double)u / (double)((u + slots - 1) / slots * slots);
-    if (x > fill + 0.04) {
-      best = k;
-      fill = x;
-    }
-  }
-  return best;
+  // wavefronts a path, as dispatched below: eight a workgroup past N = 28 (complex N = 24)
+  const int nwp = (NG > (c->ctrial ? 6 : 7) ? 8 : 4) / pp;
+  return plan_splits(((long)nw * c->P + pp - 1) / pp, NG <= 3 ? 1024 : NG <= 7 ? 512 : 256,
+                     (c->G + GV) / GV, 4, nwp);
 }
 
 hipError_t launch_contract_q(const afqmc_ctx_s* c, int nw, int nsplit, const double* phiT,

@@ -36,6 +36,7 @@
 #include <type_traits>
 
 #include "afqmc_internal.h"
+#include "contract_sum.h"
 #include "dev_common.h"
 
 namespace {
@@ -197,7 +198,7 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
   float* sF = reinterpret_cast<float*>(sY + BCP * NP * YT);           // [BCP][re, im][NT][PW]
   float* sD = sF + BCP * 2 * NT * PW;                                   // [BCP][BFL][re, im][NWV*16]
   double* sE = reinterpret_cast<double*>(sD + BCP * BFL * 2 * NWV * 16);  // [BCP][NWV][2]
-  double* sT = sE + BCP * NWV * 2;                                         // [NWT][4]
+  double* sT = sE + BCP * NWV * 2;                                         // [NWT][2]
 
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int g = lane >> 4, c = lane & 15;
@@ -214,12 +215,10 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
   const bool active = valid && !__builtin_isinf(logov[2 * sc]);
   // this workgroup's range of the vectors, in whole blocks of BFL (so the first has an even
   // number); the last range has h1' (slab G) too
-  const int nblk = (G + BFL - 1) / BFL;
-  const int gbeg =
-      RANGES ? __builtin_amdgcn_readfirstlane((int)blockIdx.y * nblk / (int)gridDim.y * BFL) : 0;
-  const int gnext = RANGES ? __builtin_amdgcn_readfirstlane(((int)blockIdx.y + 1) * nblk /
-                                                            (int)gridDim.y * BFL)
-                           : G;
+  const int nfl = (G + BFL - 1) / BFL;
+  block_range rng(nfl, RANGES ? blockIdx.y : 0, RANGES ? gridDim.y : 1, nfl);  // blocks of BFL vectors
+  const int gbeg = RANGES ? __builtin_amdgcn_readfirstlane(rng.begin() * BFL) : 0;
+  const int gnext = RANGES ? __builtin_amdgcn_readfirstlane(rng.b.begin(rng.last) * BFL) : G;
   const int gend = !RANGES || gnext >= G ? G : gnext - 1;
 
   // Y^T tile index of 4-row group grp, column col: groups 2p and 2p + 1 of a column side
@@ -300,7 +299,11 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
   V4* Yb = sY + pw * NP * YT;  // the path's Y^T tile
   float* Fp = sF + (size_t)pw * 2 * NT * PW;
   float* Dp = sD + (size_t)pw * BFL * 2 * NWV * 16;
-  double ex_re = 0.0, ex_im = 0.0, vb2_re = 0.0, vb2_im = 0.0, e1_re = 0.0, e1_im = 0.0;
+  double ex_re = 0.0, ex_im = 0.0;  // -2 times this lane's share of E_p in the block of vectors
+  auto block_end = [&]() {
+    rng.add(-0.5 * ex_re, -0.5 * ex_im, epart, wv, NWV, n_samples, s, valid, active);
+    ex_re = ex_im = 0.0;
+  };
   for (int gam = gbeg; gam <= gend; ++gam) {
     const int b = NB == 2 ? (gam & 1) : 0;
     // stage 1: Y^T tiles (tp, ct) from the shared slab
@@ -415,8 +418,8 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
       __syncthreads();
       if (wv == 0 && lane == 0) {
         for (int w = 0; w < NWV; ++w) {
-          e1_re += sE[(pw * NWV + w) * 2];
-          e1_im += sE[(pw * NWV + w) * 2 + 1];
+          ex_re -= 2.0 * sE[(pw * NWV + w) * 2];
+          ex_im -= 2.0 * sE[(pw * NWV + w) * 2 + 1];
         }
       }
       break;
@@ -475,55 +478,49 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
     ex_re += (double)xr;
     ex_im += (double)xi;
     // every BFL vectors: wavefront 0 of each path reduces its staged diagonals to vb_g
-    // four lanes per sum (vector gl, part re/im), NWV * 4 staged values each, summed in FP64
-    if ((gam % BFL == BFL - 1 || gam == G - 1) && wv == 0 && valid) {
-      static_assert(BFL * 2 * 4 == 64, "one lane quad per staged vector and part");
-      constexpr int QN = NWV * 16, QL = QN / 4;
-      const int cnt = gam % BFL + 1, g0 = gam - gam % BFL;
-      const int gl = lane >> 3, part = (lane >> 2) & 1, qq = lane & 3;
-      double v = 0.0;
-      if (gl < cnt) {
-        const fx4* src = reinterpret_cast<const fx4*>(Dp + (gl * 2 + part) * QN + qq * QL);
+    // four lanes per sum (vector gl, part re/im), NWV * 4 staged values each, summed in FP64;
+    // and the block of E_p's sum ends (the last one with h1')
+    if (gam % BFL == BFL - 1 || gam == G - 1) {
+      if (wv == 0 && valid) {
+        static_assert(BFL * 2 * 4 == 64, "one lane quad per staged vector and part");
+        constexpr int QN = NWV * 16, QL = QN / 4;
+        const int cnt = gam % BFL + 1, g0 = gam - gam % BFL;
+        const int gl = lane >> 3, part = (lane >> 2) & 1, qq = lane & 3;
+        double v = 0.0;
+        if (gl < cnt) {
+          const fx4* src = reinterpret_cast<const fx4*>(Dp + (gl * 2 + part) * QN + qq * QL);
 #pragma unroll
-        for (int e = 0; e < QL / 4; ++e) {
-          const fx4 x = src[e];
-          v += ((double)x[0] + (double)x[1]) + ((double)x[2] + (double)x[3]);
+          for (int e = 0; e < QL / 4; ++e) {
+            const fx4 x = src[e];
+            v += ((double)x[0] + (double)x[1]) + ((double)x[2] + (double)x[3]);
+          }
+        }
+        v += dpp_f64<0xB1>(v);  // quad sum
+        v += dpp_f64<0x4E>(v);
+        const double vi = __shfl_down(v, 4, 64);
+        if ((lane & 7) == 0 && gl < cnt) {
+          ex_re -= fma(v, v, -(vi * vi));  // the same in both forms of the kernel
+          ex_im = fma(-2.0 * v, vi, ex_im);
+          double* o = vb + ((size_t)s * G + g0 + gl) * 2;
+          o[0] = v;
+          o[1] = vi;
         }
       }
-      v += dpp_f64<0xB1>(v);  // quad sum
-      v += dpp_f64<0x4E>(v);
-      const double vi = __shfl_down(v, 4, 64);
-      if ((lane & 7) == 0 && gl < cnt) {
-        vb2_re += v * v - vi * vi;
-        vb2_im += 2.0 * v * vi;
-        double* o = vb + ((size_t)s * G + g0 + gl) * 2;
-        o[0] = v;
-        o[1] = vi;
-      }
+      if (gam < G - 1) block_end();
     }
   }
-  // totals per path: ex from every lane of its wavefronts, vb^2 from its wavefront 0
-  ex_re = wave_sum(ex_re);
-  ex_im = wave_sum(ex_im);
-  vb2_re = wave_sum(vb2_re);
-  vb2_im = wave_sum(vb2_im);
-  if (lane == 0) {
-    sT[wave * 4 + 0] = ex_re;
-    sT[wave * 4 + 1] = ex_im;
-    sT[wave * 4 + 2] = vb2_re;
-    sT[wave * 4 + 3] = vb2_im;
-  }
+  if (gend == G) block_end();
+  const double2 e_wave = rng.total();  // with all lanes active
+  if (lane == 0) *reinterpret_cast<double2*>(sT + wave * 2) = e_wave;
   __syncthreads();
-  if (valid && wv == 0 && lane == 0) {
+  if (!RANGES && valid && wv == 0 && lane == 0) {
     double xr = 0.0, xi = 0.0;
     for (int w = 0; w < NWV; ++w) {
-      xr += sT[(pw * NWV + w) * 4 + 0];
-      xi += sT[(pw * NWV + w) * 4 + 1];
+      xr += sT[(wave + w) * 2];
+      xi += sT[(wave + w) * 2 + 1];
     }
-    const double br = sT[pw * NWV * 4 + 2], bi = sT[pw * NWV * 4 + 3];
-    double* o = epart + ((RANGES ? (size_t)blockIdx.y * n_samples : 0) + s) * 2;
-    o[0] = active ? e1_re + 0.5 * br - 0.5 * xr : 0.0;
-    o[1] = active ? e1_im + 0.5 * bi - 0.5 * xi : 0.0;
+    epart[(size_t)s * 2] = active ? xr : 0.0;
+    epart[(size_t)s * 2 + 1] = active ? xi : 0.0;
   }
   if (valid && !active && wv == 0)
     for (int q = 2 * gbeg + lane; q < 2 * min(gend + 1, G); q += 64) vb[(size_t)s * G * 2 + q] = 0.0;
@@ -539,7 +536,7 @@ size_t lds_bytes_s(int KT, int NTC, int NCP, int FM, int BCP) {
   b += (size_t)BCP * (MTP / 4) * NT * (FM == FM_BF16X3 ? 16 : 8);  // Y^T tiles
   b += (size_t)BCP * NT * (16 * NCP + 4) * 2 * 4;     // packed f (FP32)
   b += (size_t)BCP * BFL * NWV * 16 * 2 * 4;          // staged diagonals (FP32)
-  b += (size_t)BCP * NWV * 2 * 8 + (size_t)BCP * NWV * 4 * 8;
+  b += (size_t)BCP * NWV * 2 * 8 * 2;
   return b;
 }
 
@@ -600,30 +597,19 @@ __global__ void k_to_bf16_op(size_t n, int MT, const double* __restrict__ src,
 
 }  // namespace
 
-// Ranges of g, for calls that do not fill one round of the chip (eight wavefronts a CU): the
-// fewest that fill the rounds to within 4 %, at least two blocks of BFL vectors to a range.
-// 40 paths of M = 96, N = 24, 384 vectors: BF16 0.80 -> 0.083 ms, split BF16 1.64 -> 0.155;
-// 200 paths of M = 80, N = 26: 0.30 -> 0.18 and 0.79 -> 0.37.  Past one round a split gained
-// little (2 % at 1.2 rounds) or lost (9 % at 5.5 rounds).  k P <= M^2 keeps the partial sums
-// within the workspace's V buffer, which holds them.
-int contract_sh_splits(const afqmc_ctx_s* c, int nw) {
+// Ranges of g, for calls that do not fill one round of the chip (eight wavefronts a CU), at
+// least two steps of BFL vectors to a range.  40 paths of M = 96, N = 24, 384 vectors: BF16
+// 0.80 -> 0.083 ms, split BF16 1.64 -> 0.155; 200 paths of M = 80, N = 26: 0.30 -> 0.18 and
+// 0.79 -> 0.37.  Past one round a split gained little (2 % at 1.2 rounds) or lost (9 % at
+// 5.5 rounds).
+contract_plan contract_sh_plan(const afqmc_ctx_s* c, int nw) {
   const int ncp = (2 * c->N + 15) / 16;
   const int bcp = bcp_for(c->precision == AFQMC_PREC_BF16 ? FM_BF16 : FM_BF16X3, ncp);
   const long units = ((long)nw * c->P + bcp - 1) / bcp;
   const long slots = 256 * (ncp * bcp < 8 ? 8 / (ncp * bcp) : 1);
-  const int nblk = (c->G + BFL - 1) / BFL;
-  int best = 1;
-  double fill = 0.0;
-  if (units > slots) return 1;
-  for (int k = 1; k <= 16 && k * 2 <= nblk && k * c->P <= c->M * c->M; ++k) {
-    const long u = units * k;
-    const double x = (double)u / (double)((u + slots - 1) / slots * slots);
-    if (x > fill + 0.04) {
-      best = k;
-      fill = x;
-    }
-  }
-  return best;
+  if (units > slots) return contract_plan();
+  const int nfl = (c->G + BFL - 1) / BFL;
+  return plan_splits(units, slots, nfl, 2, ncp, nfl);
 }
 
 hipError_t launch_contract_sh(const afqmc_ctx_s* c, int nw, int nsplit, const double* phiT,

@@ -375,16 +375,6 @@ hipError_t launch_zero_int(const afqmc_ctx_s* c, int n, int* p) {
 // 146 -> 76 us.
 namespace {
 
-// sum over the wavefront, all 64 lanes active: DPP moves within each 16-lane row, then the
-// rows' sums by readlane
-__device__ __forceinline__ double wave_sum_full(double v) {
-  v += dpp_f64<0xB1>(v);
-  v += dpp_f64<0x4E>(v);
-  v += dpp_f64<0x141>(v);
-  v += dpp_f64<0x140>(v);
-  return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
-}
-
 // KW: lanes that take a column each in the inner products (N <= KW); the 64 / KW groups of a
 // wavefront take rows of their own.  BOTH: one workgroup does both spins, a wavefront each,
 // and shifts the log-overlaps itself.

@@ -110,3 +110,80 @@ def test_back_propagation(shape):
         torch.cuda.synchronize()
         out.append((bra, th, lb, rho))
     same(*out, few)
+
+
+# (M, N, vectors, hidden, paths, walkers, of the small call, precision, Ising)
+STEPS = [(72, 18, 40, 9, 2, 150, 3, 0, False), (64, 16, 64, 8, 4, 300, 5, 0, False),
+         (24, 6, 96, 8, 4, 300, 2, 0, False), (8, 2, 16, 4, 8, 200, 9, 0, True),
+         (70, 22, 50, 6, 2, 150, 3, 1, False), (24, 10, 40, 6, 4, 200, 3, 1, False),
+         (70, 22, 50, 6, 2, 150, 3, 2, False), (40, 9, 40, 6, 4, 150, 3, 3, False)]
+
+
+@pytest.mark.parametrize("shape", STEPS)
+def test_steps(shape):
+    M, N, G, K, P, many, few, prec, ising = shape
+    say("steps", shape)
+    s = ai.workload(0)[0] if ising else ai.small_gaussian(M=M, N=N, n_chol=G, K=K, seed=M + N)
+    A, ctx = context(s, P, many, precision=prec)
+    from paper_2505_18519_amd import driver as D
+    out = []
+    for n in (many, few):
+        w, est = D.init_walkers(ctx, s.phi0, n, 3), torch.zeros(2, device="cuda", dtype=torch.float64)
+        for i in range(3):
+            D.step(ctx, w, 3, i, est, n_qr=2)
+        torch.cuda.synchronize()
+        out.append((w.phi, w.w, w.y, w.phiT, w.logov, w.eloc, w.xbar))
+    same(*out, few)
+
+
+# (M, N, vectors, paths, walkers, of the small call, precision): FP64 on either kernel, FP32,
+# BF16 and split BF16, with calls that split the vectors over several workgroups differently;
+# 1100 paths of N = 30 split where the workspace has room, not in the fixed scratch
+CONTRACTIONS = [(64, 16, 100, 4, 600, 3, 0), (60, 13, 70, 4, 300, 1, 0), (24, 6, 97, 4, 300, 5, 0),
+                (45, 11, 180, 4, 333, 30, 0), (72, 18, 66, 3, 300, 11, 0),
+                (96, 24, 130, 4, 130, 3, 0), (142, 35, 75, 3, 90, 2, 0), (40, 30, 192, 1, 1100, 3, 0),
+                (33, 7, 100, 4, 300, 2, 1), (64, 15, 63, 4, 300, 9, 1), (96, 24, 70, 4, 300, 2, 1),
+                (128, 32, 67, 4, 130, 3, 1),
+                (40, 6, 65, 4, 520, 3, 2), (96, 20, 50, 2, 600, 9, 2), (128, 32, 100, 4, 150, 3, 2),
+                (40, 12, 65, 4, 520, 3, 3), (64, 30, 51, 2, 600, 9, 3)]
+
+
+@pytest.mark.parametrize("shape", CONTRACTIONS)
+def test_contraction(shape):
+    M, N, G, P, many, few, prec = shape
+    say("contraction", shape)
+    s = ai.small_gaussian(M=M, N=N, n_chol=G, K=4, seed=M + N)
+    A, ctx = context(s, P, many, precision=prec)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    phiT, theta = normal(gen, many, P, M, N), normal(gen, many, P, 2, M, N, cplx=True) / M
+    out = []
+    for n in (many, few):
+        check_contraction(A, ctx, n, G, P, phiT, theta, out)
+    same(*out, few)
+
+
+@pytest.mark.parametrize("shape", [(20, 5, 60, 4, 200, 2), (58, 22, 90, 2, 300, 3)])
+def test_complex_contraction(shape):
+    M, N, G, P, many, few = shape
+    say("complex contraction", shape)
+    s = ai.imaginary_time_trial(ai.small_gaussian(M=M, N=N, n_chol=G, K=4, seed=M + N), 1, 0.02,
+                                n_gen=4)
+    A, ctx = context(s, P, many)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    phiT = normal(gen, many, P, M, N, cplx=True)
+    theta = normal(gen, many, P, 2, M, N, cplx=True) / M
+    out = []
+    for n in (many, few):
+        check_contraction(A, ctx, n, G, P, phiT, theta, out)
+    same(*out, few)
+
+
+def check_contraction(A, ctx, n, G, P, phiT, theta, out):
+    args = phiT[:n].contiguous(), theta[:n].contiguous(), zeros(n, P)
+    el, ep, xb = zeros(n), zeros(n, P), zeros(n, G)
+    A.afqmc_local_energy(ctx, n, *args, el, ep, xb)
+    st = zeros(n), zeros(n, P), zeros(n, G)
+    A.afqmc_local_energy_static(ctx, n, *args, *st)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(st, (el, ep, xb)))
+    out.append((el, ep, xb))
