@@ -13,7 +13,7 @@
 
 // Blocks: up to 48, which 1, 2, 3, 4, 6, 8, 12 and 16 workgroups share evenly (by the count of
 // granules, 16 blocks leave one call in four 5 % or more behind an even split, 48 one in
-// twenty).  The sums at their ends cost whole-chip calls up to 1 % at M >= 64, 2 to 5 % at
+// twenty).  The sums at their ends cost whole-chip calls up to 1 % at M >= 64, up to 3 % at
 // M = 24.
 constexpr int kSumBlocks = 48;
 constexpr int kMaxWaves = 8;  // wavefronts that share a path, at most
@@ -34,7 +34,7 @@ struct contract_plan {
 
 // The fewest workgroups along the vectors (up to 16, each at least `least` granules) within
 // 4 % of the shortest time: rounds of the `slots` workgroups that the chip holds times the
-// longest range (the mean range where the granules are so many that ranges differ little).
+// longest range (the mean range where the blocks are so many that ranges differ little).
 inline contract_plan plan_splits(long units, long slots, int granules, int least, int waves,
                                  int most = kSumBlocks) {
   const vec_blocks b(granules, most);
@@ -44,7 +44,7 @@ inline contract_plan plan_splits(long units, long slots, int granules, int least
   double best = 1e300;
   for (int k = 1; k <= 16 && k <= b.n && (k == 1 || k * least <= granules); ++k) {
     double len = (double)granules / k;
-    if (granules <= kSumBlocks)
+    if (b.n < kSumBlocks)
       for (int i = 0; i < k; ++i)
         len = std::max(len, (double)(b.begin((i + 1) * b.n / k) - b.begin(i * b.n / k)));
     const double t = (double)((units * k + slots - 1) / slots) * len;

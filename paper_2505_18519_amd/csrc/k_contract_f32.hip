@@ -41,7 +41,14 @@
 
 namespace {
 
-constexpr int GRP = 2;  // groups of vectors in a granule of the sum over them
+// Blocks of the sum over the vectors: at least four groups each (the sum at a block's end
+// takes 0.3 us, a group of M = 24, N = 6 1.1), in a number that the likely ranges share evenly
+__host__ __device__ constexpr int sum_blocks(int ngrp) {
+  constexpr int n[] = {48, 24, 12, 8, 6, 4, 3, 2};
+  for (int q : n)
+    if (4 * q <= ngrp) return q;
+  return 1;
+}
 
 template <int KT, int T>
 struct Shape {
@@ -104,8 +111,8 @@ k_contract_f32(int n_samples, int M, int N, int G, const fx4* Lop,
   }
   // G vectors and h1' in groups of two; this workgroup's range of them
   const int ngrp = (G + 2) / 2;
-  block_range rng((ngrp + GRP - 1) / GRP, blockIdx.y, gridDim.y);
-  const int grp0 = rng.begin() * GRP, grp1 = min(rng.b.begin(rng.last) * GRP, ngrp);
+  block_range rng(ngrp, blockIdx.y, gridDim.y, sum_blocks(ngrp));
+  const int grp0 = rng.begin(), grp1 = rng.b.begin(rng.last);
   // operands of one row tile, read ahead: a[t] is reloaded right after its products
   fx4 a[KT];
   const fx4* Lw = Lop + (size_t)min(2 * grp0 + v1, G) * SLAB;
@@ -221,7 +228,7 @@ k_contract_f32(int n_samples, int M, int N, int G, const fx4* Lop,
     }
   };
   stage1(grp0);
-  int bend = rng.end() * GRP;
+  int bend = rng.end();
   for (int grp = grp0; grp < grp1; ++grp) {
     __syncthreads();
 #pragma unroll
@@ -254,10 +261,10 @@ k_contract_f32(int n_samples, int M, int N, int G, const fx4* Lop,
     if (!late) trace(grp);
     if (grp + 1 < grp1) stage1(grp + 1);
     if (late) trace(grp);
-    if (grp + 1 == bend || grp + 1 == ngrp) {
+    if (grp + 1 == bend) {
       rng.add(e_re, e_im, epart, w1, T, n_samples, s, valid, active);
       e_re = e_im = 0.0;
-      bend = rng.end() * GRP;
+      bend = rng.end();
     }
   }
   if (Sh::NPR == 2 && pair == 0) __syncthreads();
@@ -310,8 +317,9 @@ __global__ void k_to_f32_op(size_t n, int MT, const double* __restrict__ src,
 // one range, 0.81 in six.
 contract_plan contract_f32_plan(const afqmc_ctx_s* c, int nw) {
   const int pp = c->N > 24 ? 2 : 4;
-  return plan_splits(((long)nw * c->P + pp - 1) / pp, c->N > 8 ? 256 : 768,
-                     ((c->G + 2) / 2 + GRP - 1) / GRP, 8 / GRP, (c->N + 7) / 8);
+  const int ngrp = (c->G + 2) / 2;
+  return plan_splits(((long)nw * c->P + pp - 1) / pp, c->N > 8 ? 256 : 768, ngrp, 8,
+                     (c->N + 7) / 8, sum_blocks(ngrp));
 }
 
 hipError_t launch_contract_f32(const afqmc_ctx_s* c, int nw, int nsplit, const double* phiT,
