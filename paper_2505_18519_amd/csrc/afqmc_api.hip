@@ -209,7 +209,7 @@ hipError_t do_overlap(const afqmc_ctx_s* c, int nw, const double* phi, const dou
   // The FP32 contraction rounds Theta to FP32: the last bits of the other kernels' inverse
   // (1e-15) would move the rounding of about one entry in 10^8 by 6e-8.  The BF16
   // forms' roundings are coarse enough (one entry in 10^10 and 10^12).
-  if (c->precision == AFQMC_PREC_FP32 && !c->ctrial && theta != nullptr && gdiag == nullptr)
+  if (overlap_by_lu(c, theta, gdiag) && (!c->small || overlap_lu_wide(c, nw)))
     return launch_overlap_lu(c, nw, phi, phiT, logov, theta);
   return c->small ? launch_overlap(c, nw, phi, phiT, logov, theta, gdiag)
                   : launch_overlap_g(c, nw, phi, phiT, logov, theta, gdiag);

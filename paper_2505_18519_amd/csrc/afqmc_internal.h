@@ -185,6 +185,14 @@ bool ising_sweep_takes(const afqmc_ctx_s* c);
 hipError_t launch_ising_sweep(const afqmc_ctx_s* c, int nw, const double* phi, double* y,
                               double* phiT, double* logov, int* nacc, uint64_t seed, uint64_t step,
                               int sweep);
+// Theta of FP32 contexts with real trials: from LU factors (k_overlap_lu.hip)
+inline bool overlap_by_lu(const afqmc_ctx_s* c, const double* theta, const double* gdiag) {
+  return c->precision == AFQMC_PREC_FP32 && !c->ctrial && theta != nullptr && gdiag == nullptr;
+}
+// small systems: a workgroup per path (k_overlap_lu) rather than two paths a wavefront
+inline bool overlap_lu_wide(const afqmc_ctx_s* c, int nw) {
+  return c->N > 8 && (long)nw * c->P < 1024;
+}
 hipError_t launch_overlap_lu(const afqmc_ctx_s* c, int nw, const double* phi, const double* phiT,
                              double* logov, double* theta);
 hipError_t launch_overlap_g(const afqmc_ctx_s* c, int nw, const double* phi, const double* phiT,

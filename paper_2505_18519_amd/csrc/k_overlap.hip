@@ -17,6 +17,13 @@
 // A zero pivot marks the path singular: l = -inf + 0i and Theta = 0, diag = 0.
 // A non-finite overlap entry gives l = NaN + NaN i (Theta and diag 0).
 //
+// FP32 contexts' Theta (the FP32 contraction rounds it to FP32, see k_overlap_lu.hip) comes
+// from an LU factorisation and triangular solves instead, unrolled over rows and columns: lane
+// (path, spin, j) solves z U = e_j, v L = z, X[j][perm[k]] = v[k].  With a workgroup per path
+// (k_overlap_lu) and here: M = 24, N = 6, 4000 paths 67 and 27 us; M = 48, N = 12, 4000 paths 108 and
+// 58; M = 64, N = 16, 4096 paths 138 and 76, but 120 paths 35 and 49: calls that leave the chip
+// part empty run there for N > 8 (overlap_lu_wide).  Both give the same bits.
+//
 // The elimination is a loop: after a step every row moves up one register, so that the
 // pivot column is always register 0 and one step's code serves all.  Unrolled over columns
 // and steps it was 82 KB of code, past the instruction cache (64 KB for two CUs), and the
@@ -107,8 +114,78 @@ __device__ __forceinline__ void eliminate(cplx (&a)[NC], int N, int lane, int& m
   argsum = atan2(pprod.im, pprod.re) + ((inv & 1) ? M_PI : 0.0);
 }
 
-// NC: columns of a row in registers (N <= NC); INV: Theta or the diagonal requested
-template <int NC, bool INV>
+// LU factors in place with partial pivoting of four matrices, 16 lanes (rows) each, the pivots,
+// their product, mystep and singular as eliminate's: the row of step k holds U from column k
+// on and L's multipliers before it
+template <int NC>
+__device__ __forceinline__ void factor(cplx (&a)[NC], int N, int lane, int& mystep, double& logabs,
+                                       double& argsum, bool& singular) {
+  const auto mul = [](cplx x, cplx y) {
+    return cmk(fma(x.re, y.re, -(x.im * y.im)), fma(x.im, y.re, x.re * y.im));
+  };
+  const auto abs2 = [](cplx x) { return fma(x.re, x.re, x.im * x.im); };
+  const auto recip = [](cplx x) {  // crecip
+    const double m = fmax(fabs(x.re), fabs(x.im));
+    const int e = (m > 0.0 && isfinite(m)) ? ilogb(m) : 0;
+    const double r = ldexp(x.re, -e), t = ldexp(x.im, -e);
+    const double d = 1.0 / fma(r, r, t * t);
+    return cmk(ldexp(r * d, -e), ldexp(-t * d, -e));
+  };
+  const int i = lane & 15;
+  bool used = i >= N;
+  mystep = -1;
+  cplx pprod = cmk(1.0, 0.0);
+  int pexp = 0, inv = 0;
+  unsigned done = 0;
+  singular = false;
+  unrolled<NC>([&](auto K) {
+    constexpr int k = decltype(K)::value;
+    if (k >= N) return;
+    double v = used ? -1.0 : abs2(a[k]);
+    if (!used && !(v >= 0.0)) v = 0.0;
+    double vm = fmax(v, dpp_f64<0xB1>(v));
+    vm = fmax(vm, dpp_f64<0x4E>(vm));
+    vm = fmax(vm, dpp_f64<0x141>(vm));
+    vm = fmax(vm, dpp_f64<0x140>(vm));
+    const unsigned cand = (unsigned)(__ballot(!used && v == vm) >> (lane & 48)) & 0xffffu;
+    const int prow = __builtin_ctz(cand | 0x10000u) & 15;  // uniform within the group
+    inv += __builtin_popcount(done >> prow);
+    done |= 1u << prow;
+    const int src = (lane & 48) + prow;
+    const cplx piv = cmk(__shfl(a[k].re, src, 64), __shfl(a[k].im, src, 64));
+    if (!(vm > 0.0)) singular = true;
+    if (i == prow) {
+      used = true;
+      mystep = k;
+    }
+    pprod = mul(pprod, piv);
+    const double mx = fmax(fabs(pprod.re), fabs(pprod.im));
+    if (mx > 0.0 && isfinite(mx)) {
+      const int ex = ilogb(mx);
+      pprod = cscale(pprod, ldexp(1.0, -ex));
+      pexp += ex;
+    }
+    const bool live = !used && !singular;
+    cplx l = cmk(0.0, 0.0);
+    if (live) {
+      l = mul(a[k], recip(piv));  // the pivot's reciprocal: one real division
+      a[k] = l;
+    }
+#pragma unroll
+    for (int j = k + 1; j < NC; ++j) {
+      const cplx pj = cmk(__shfl(a[j].re, src, 64), __shfl(a[j].im, src, 64));
+      if (live) a[j] = cfms(a[j], l, pj);
+    }
+  });
+  logabs = fma((double)pexp, M_LN2, 0.5 * log(abs2(pprod)));
+  argsum = atan2(pprod.im, pprod.re) + ((inv & 1) ? M_PI : 0.0);
+}
+
+enum { OV_DET = 0, OV_INV = 1, OV_LU = 2 };
+
+// NC: columns of a row in registers (N <= NC).  MODE: log-overlaps only, or with Theta or the
+// diagonal from the inverse (OV_INV) or Theta from LU factors (OV_LU)
+template <int NC, int MODE>
 __global__ void __launch_bounds__(OV_WAVES * 64, 2)
 k_overlap(int n_samples, int P, int M, int N, const double* __restrict__ phi,
           const double* __restrict__ phiT, double* __restrict__ logov, double* __restrict__ theta,
@@ -178,7 +255,10 @@ k_overlap(int n_samples, int P, int M, int N, const double* __restrict__ phi,
   cplx scale;
   double logabs, argsum;
   bool singular;
-  eliminate<NC, INV>(a, N, lane, mystep, scale, logabs, argsum, singular);
+  if constexpr (MODE == OV_LU)
+    factor<NC>(a, N, lane, mystep, logabs, argsum, singular);
+  else
+    eliminate<NC, MODE == OV_INV>(a, N, lane, mystep, scale, logabs, argsum, singular);
 
   // both spins' results to the lanes of the path's first spin
   const double la_dn = __shfl(logabs, (lane & 32) + 16, 64);
@@ -198,17 +278,52 @@ k_overlap(int n_samples, int P, int M, int N, const double* __restrict__ phi,
       o[1] = argsum + ar_dn;
     }
   }
-  if constexpr (!INV) return;
+  if constexpr (MODE == OV_DET) return;
 
   // 3. X^s = (A^s)^{-1}: the row of step k is X's row k, and register NC - N + m its column
   //    perm[m]; the rest is zero
   const unsigned long long deadm = __ballot(sing_any || nf_any);
   if (mystep >= 0) s_perm[wave][g][mystep] = i;
+  if constexpr (MODE == OV_LU) {
+    if (mystep >= 0)
+#pragma unroll
+      for (int j = 0; j < NC; ++j) {
+        s_lu[wave][g][mystep][j][0] = a[j].re;
+        s_lu[wave][g][mystep][j][1] = a[j].im;
+      }
+    fence();
+    auto lu = [&](int k, int j) { return cmk(s_lu[wave][g][k][j][0], s_lu[wave][g][k][j][1]); };
+#pragma unroll
+    for (int j = 0; j < NC; ++j) a[j] = cmk(j == i ? 1.0 : 0.0, 0.0);
+#pragma unroll
+    for (int j = 0; j < NC; ++j)
+      if (j < N) {
+#pragma unroll
+        for (int k = 0; k < j; ++k) a[j] = cfms(a[j], a[k], lu(k, j));
+        a[j] = cdiv(a[j], lu(j, j));
+      }
+#pragma unroll
+    for (int j = NC - 1; j >= 0; --j)
+      if (j < N)
+#pragma unroll
+        for (int k = j + 1; k < NC; ++k)
+          if (k < N) a[j] = cfms(a[j], a[k], lu(k, j));
+    fence();  // the factors are read
+  }
   if (i < NC)
 #pragma unroll
     for (int j = 0; j < NC; ++j) s_lu[wave][g][i][j][0] = s_lu[wave][g][i][j][1] = 0.0;
   fence();
-  if (mystep >= 0) {
+  if constexpr (MODE == OV_LU) {
+    if (i < N)
+#pragma unroll
+      for (int k = 0; k < NC; ++k)
+        if (k < N) {
+          const int col = s_perm[wave][g][k] & (NC - 1);
+          s_lu[wave][g][i][col][0] = a[k].re;
+          s_lu[wave][g][i][col][1] = a[k].im;
+        }
+  } else if (mystep >= 0) {
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
       const int m = j - (NC - N);
@@ -440,7 +555,9 @@ template <int NC>
 hipError_t launch_nc(const afqmc_ctx_s* c, int nw, const double* phi, const double* phiT,
                      double* logov, double* theta, double* gdiag) {
   const int n = nw * c->P;
-  auto kern = theta != nullptr || gdiag != nullptr ? k_overlap<NC, true> : k_overlap<NC, false>;
+  auto kern = theta == nullptr && gdiag == nullptr ? k_overlap<NC, OV_DET>
+              : overlap_by_lu(c, theta, gdiag)     ? k_overlap<NC, OV_LU>
+                                                   : k_overlap<NC, OV_INV>;
   hipLaunchKernelGGL(kern, dim3((n + 2 * OV_WAVES - 1) / (2 * OV_WAVES)), dim3(OV_WAVES * 64), 0,
                      c->stream, n, c->P, c->M, c->N, phi, phiT, logov, theta, gdiag);
   return hipGetLastError();

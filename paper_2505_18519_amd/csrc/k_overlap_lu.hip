@@ -1,10 +1,11 @@
-// Theta and log-overlaps of FP32 contexts with real trials (N <= 32): the quantities of
-// k_overlap and k_overlap_g, with Theta from an LU factorisation with partial pivoting and
-// triangular solves, z U = e_j, v L = z, X[j][perm[k]] = v[k] for the unit rows e_j.  The
+// Theta and log-overlaps of FP32 contexts with real trials (N <= 32), past M = 64 or N = 16
+// and for few paths (large calls of small systems: k_overlap): the quantities of k_overlap
+// and k_overlap_g, with Theta from an LU factorisation with partial pivoting and triangular
+// solves, z U = e_j, v L = z, X[j][perm[k]] = v[k] for the unit rows e_j.  The
 // FP32 contraction rounds Theta to FP32, so Theta's last bits are kept as they are here:
 // the other kernels' Gauss-Jordan inverse (at M = 96, N = 24, 8192 paths 556 us instead of
-// 959, of 22.5 ms with the contraction; at M = 24, N = 6, 4000 paths 35 instead of 67, of
-// 0.23 ms) moves the rounding of a few entries in 4 10^7 by 6e-8.
+// 959, of 22.5 ms with the contraction) moves the rounding of a few entries in 4 10^7 by
+// 6e-8, and with it an energy by 1e-9.
 #include "afqmc_internal.h"
 #include "dev_common.h"
 
