@@ -312,14 +312,21 @@ __global__ void k_to_f32_op(size_t n, int MT, const double* __restrict__ src,
 
 }  // namespace
 
+// 8-wide column tiles a path: with three past M = 96 a workgroup's two pairs of paths would need
+// 162 KB of LDS and more, so that four, with one pair, take those sizes (the fourth is padding)
+static int tiles(const afqmc_ctx_s* c) {
+  const int T = (c->N + 7) / 8;
+  return T == 3 && c->MT > 96 ? 4 : T;
+}
+
 // Ranges of g (slots: one workgroup a CU, or three of the small ones of N <= 8; at least
 // eight groups of vectors to a range).  256 paths of M = 96, N = 24 (64 workgroups): 2.8 ms in
 // one range, 0.81 in six.
 contract_plan contract_f32_plan(const afqmc_ctx_s* c, int nw) {
-  const int pp = c->N > 24 ? 2 : 4;
+  const int T = tiles(c), pp = T == 4 ? 2 : 4;
   const int ngrp = (c->G + 2) / 2;
-  return plan_splits(((long)nw * c->P + pp - 1) / pp, c->N > 8 ? 256 : 768, ngrp, 8,
-                     (c->N + 7) / 8, sum_blocks(ngrp));
+  return plan_splits(((long)nw * c->P + pp - 1) / pp, T > 1 ? 256 : 768, ngrp, 8, T,
+                     sum_blocks(ngrp));
 }
 
 hipError_t launch_contract_f32(const afqmc_ctx_s* c, int nw, int nsplit, const double* phiT,
@@ -327,7 +334,7 @@ hipError_t launch_contract_f32(const afqmc_ctx_s* c, int nw, int nsplit, const d
                                double* epart) {
   if (nw <= 0) return hipSuccess;
   if (c->d_Lpad32 == nullptr) return hipErrorInvalidValue;
-  const int n = nw * c->P, T = (c->N + 7) / 8;
+  const int n = nw * c->P, T = tiles(c);
 #define AFQMC_CF(KK, TT)            \
   if (c->MT == 16 * KK && T == TT) \
     return launch_f32<KK, TT>(c, n, nsplit, phiT, theta, logov, vb, epart);
@@ -339,7 +346,7 @@ hipError_t launch_contract_f32(const afqmc_ctx_s* c, int nw, int nsplit, const d
   AFQMC_CF(2, 4) AFQMC_CF(3, 4) AFQMC_CF(4, 4)
   AFQMC_CF(5, 4) AFQMC_CF(6, 4) AFQMC_CF(7, 4) AFQMC_CF(8, 4)
 #undef AFQMC_CF
-  return hipErrorInvalidValue;  // 17 <= N <= 24 past M = 96
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_to_f32_op(const afqmc_ctx_s* c, size_t n, const double* src, float* dst) {
