@@ -140,10 +140,26 @@ struct Form {
 // staged for the transpose in FP32 (its products are FP32); the diagonals are
 // staged in FP32 and flush every BFL vectors, four lanes per sum.
 constexpr int BFL = 8;  // vectors per flush of the staged diagonals
+constexpr size_t kMaxLds = 160 * 1024;  // a CU's
 
-// Paths per workgroup.  Four when a path has three wavefronts (twelve
-// wavefronts put three on every SIMD instead of two on some and one on
-// others).  Plain BF16 with four wavefronts per path (N = 25 .. 32): one path,
+// slabs: buffers x parts x bytes per entry = 2 x 1 x 2 (BF16 shared; none for one
+// path) or 1 x 2 x 2 (split BF16), over MT x MTP entries (MTP: k padded to whole
+// blocks); Y^T tiles: parts x bytes per 4-row group = 1 x 8 (BF16), 2 x 8 (split BF16)
+constexpr size_t lds_bytes_s(int KT, int NTC, int NCP, int FM, int BCP) {
+  const int MT = 16 * KT, NT = 16 * NTC, NWV = NCP;
+  const int KB = 32, MTP = (MT + KB - 1) / KB * KB;
+  size_t b = BCP == 1 ? 0 : (size_t)4 * MT * MTP;  // slabs (none with one path per workgroup)
+  b += (size_t)BCP * (MTP / 4) * NT * (FM == FM_BF16X3 ? 16 : 8);  // Y^T tiles
+  b += (size_t)BCP * NT * (16 * NCP + 4) * 2 * 4;     // packed f (FP32)
+  b += (size_t)BCP * BFL * NWV * 16 * 2 * 4;          // staged diagonals (FP32)
+  b += (size_t)BCP * NWV * 2 * 8 * 2;
+  return b;
+}
+
+// Paths per workgroup.  Four when a path has three wavefronts (twelve wavefronts put three
+// on every SIMD instead of two on some and one on others), two past M = 96 (BF16: 112),
+// where four need more LDS than a CU has.  Plain BF16 with four wavefronts per path
+// (N = 25 .. 32): one path,
 // with no slab in LDS: each wavefront loads its own stage-1 A operands of
 // vector g + 1 from global memory (L2) into registers during vector g, a whole
 // vector ahead of their use, and two independent workgroups (about 30 KB of
@@ -151,7 +167,10 @@ constexpr int BFL = 8;  // vectors per flush of the staged diagonals
 // conversion, transpose and trace phase.  Two paths per workgroup would share
 // the slab through LDS but run every phase of all eight wavefronts in step.
 // Otherwise two.
-constexpr int bcp_for(int fm, int ncp) { return ncp == 3 ? 4 : (fm == FM_BF16 && ncp == 4) ? 1 : 2; }
+constexpr int bcp_for(int fm, int ncp, int kt) {
+  if (ncp == 3) return lds_bytes_s(kt, 2, 3, fm, 4) <= kMaxLds ? 4 : 2;
+  return fm == FM_BF16 && ncp == 4 ? 1 : 2;
+}
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef __attribute__((address_space(1))) void* gbl_ptr_t;
@@ -526,20 +545,6 @@ k_contract_sh(int n_samples, int M, int N, int G, const void* __restrict__ Lop,
     for (int q = 2 * gbeg + lane; q < 2 * min(gend + 1, G); q += 64) vb[(size_t)s * G * 2 + q] = 0.0;
 }
 
-// slabs: buffers x parts x bytes per entry = 2 x 1 x 2 (BF16 shared; none for one
-// path) or 1 x 2 x 2 (split BF16), over MT x MTP entries (MTP: k padded to whole
-// blocks); Y^T tiles: parts x bytes per 4-row group = 1 x 8 (BF16), 2 x 8 (split BF16)
-size_t lds_bytes_s(int KT, int NTC, int NCP, int FM, int BCP) {
-  const int MT = 16 * KT, NT = 16 * NTC, NWV = NCP;
-  const int KB = 32, MTP = (MT + KB - 1) / KB * KB;
-  size_t b = BCP == 1 ? 0 : (size_t)4 * MT * MTP;  // slabs (none with one path per workgroup)
-  b += (size_t)BCP * (MTP / 4) * NT * (FM == FM_BF16X3 ? 16 : 8);  // Y^T tiles
-  b += (size_t)BCP * NT * (16 * NCP + 4) * 2 * 4;     // packed f (FP32)
-  b += (size_t)BCP * BFL * NWV * 16 * 2 * 4;          // staged diagonals (FP32)
-  b += (size_t)BCP * NWV * 2 * 8 * 2;
-  return b;
-}
-
 template <int KT, int NTC, int NCP, int FM, bool FULL, int BCP>
 hipError_t launch_sh(const afqmc_ctx_s* c, int nw, int nsplit, const void* L, const void* L_lo,
                       const double* phiT, const double* theta, const double* logov, double* vb,
@@ -564,7 +569,7 @@ hipError_t dispatch_s(const afqmc_ctx_s* c, int nw, int nsplit, const void* L, c
   const bool full = c->N == 16 * NTC;
 #define AFQMC_BS(KK, NC, NP, FL)                           \
   if (KT == KK && NTC == NC && NCP == NP && full == FL) \
-    return launch_sh<KK, NC, NP, FM, FL, bcp_for(FM, NP)>(c, nw, nsplit, L, L_lo, phiT, theta, logov, vb, epart);
+    return launch_sh<KK, NC, NP, FM, FL, bcp_for(FM, NP, KK)>(c, nw, nsplit, L, L_lo, phiT, theta, logov, vb, epart);
 #define AFQMC_BS1(KK) AFQMC_BS(KK, 1, 1, false) AFQMC_BS(KK, 1, 2, false) AFQMC_BS(KK, 1, 2, true)
 #define AFQMC_BS2(KK) AFQMC_BS(KK, 2, 3, false) AFQMC_BS(KK, 2, 4, false) AFQMC_BS(KK, 2, 4, true)
   AFQMC_BS1(1) AFQMC_BS1(2) AFQMC_BS1(3) AFQMC_BS1(4)
@@ -604,7 +609,7 @@ __global__ void k_to_bf16_op(size_t n, int MT, const double* __restrict__ src,
 // 5.5 rounds).
 contract_plan contract_sh_plan(const afqmc_ctx_s* c, int nw) {
   const int ncp = (2 * c->N + 15) / 16;
-  const int bcp = bcp_for(c->precision == AFQMC_PREC_BF16 ? FM_BF16 : FM_BF16X3, ncp);
+  const int bcp = bcp_for(c->precision == AFQMC_PREC_BF16 ? FM_BF16 : FM_BF16X3, ncp, c->MT / 16);
   const long units = ((long)nw * c->P + bcp - 1) / bcp;
   const long slots = 256 * (ncp * bcp < 8 ? 8 / (ncp * bcp) : 1);
   if (units > slots) return contract_plan();

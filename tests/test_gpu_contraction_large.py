@@ -24,7 +24,7 @@ def dev(x):
     return torch.as_tensor(np.ascontiguousarray(x)).cuda()
 
 
-@pytest.mark.parametrize("prec", [1])
+@pytest.mark.parametrize("prec", [1, 2, 3])
 @pytest.mark.parametrize("shape", SHAPES)
 def test_edges(shape, prec):
     if not torch.cuda.is_available():
