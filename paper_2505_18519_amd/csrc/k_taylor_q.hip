@@ -14,6 +14,8 @@
 // M = 72, N = 18, 700 walkers: 701 -> 392 us (16 -> 28 TFLOP/s of the unpadded products);
 // M = 142, N = 35, 300 walkers, the whole move 2.72 -> 2.16 ms; M = 80, N = 21, 50 walkers
 // of 5 blocks, 20 terms of back-propagation, 5.48 -> 3.24 ms.
+#include <algorithm>
+
 #include "afqmc_internal.h"
 #include "dev_common.h"
 
@@ -155,34 +157,65 @@ k_taylor_q(int n, int M, int N, int n_taylor, int spins, int nct, int parts,
       if (okc && row_ok(t, r)) out[(size_t)(16 * t + 4 * r + g) * 2 * N] = acc[t][r];
 }
 
+// Workgroups and their wavefronts for n V of `spins` blocks: up to five column tiles in one
+// workgroup, more in fours (3 or 4 wavefronts active)
+struct q_shape {
+  int nct, nwv, parts, active;
+  q_shape(int N, int spins)
+      : nct((spins * N + 7) / 8),
+        nwv(nct <= 5 ? nct : 4),
+        parts((nct + nwv - 1) / nwv),
+        active((nct + parts - 1) / parts) {}
+};
+
 template <int KT>
 hipError_t launch_q(const afqmc_ctx_s* c, int n, int spins, int n_taylor, const double* vmat,
                     const double* El, const double* Er, const double* src, int src_ws,
                     double* dst) {
-  // up to five column tiles in one workgroup, more in fours (3 or 4 wavefronts active)
-  const int nct = (spins * c->N + 7) / 8, nwv = nct <= 5 ? nct : 4, parts = (nct + nwv - 1) / nwv;
+  const q_shape q(c->N, spins);
   const size_t lds = (size_t)2 * panel_size(c->M) * 16;
   auto kern = k_taylor_q<KT>;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(n * parts), dim3(64 * nwv), lds, c->stream, n, c->M, c->N,
-                     n_taylor, spins, nct, parts, vmat, El, Er, src, src_ws, dst);
+  hipLaunchKernelGGL(kern, dim3(n * q.parts), dim3(64 * q.nwv), lds, c->stream, n, c->M, c->N,
+                     n_taylor, spins, q.nct, q.parts, vmat, El, Er, src, src_ws, dst);
   return hipGetLastError();
 }
 
 }  // namespace
 
-// Against k_taylor_g by the products each runs for a V: this one wins from 1.15 times
-// fewer on (N = 24, M = 96: 1.33, move 1043 -> 945 us; N = 25, M = 100: 1.28, 654 -> 633),
-// not at equal counts (N = 32, M = 128: 1512 -> 1572; N = 16, M = 64 slices 920 -> 1160), and
-// not where a V gives too few wavefronts to cover the chip (M = 128, N = 8, 30 walkers: 207
-// -> 337 us: there a block's row tiles are the parallel part).  Both give the same bits, so
-// that a walker does not depend on how many others share the call.
+namespace {
+// The time of `groups` workgroups of w wavefronts on the chip's 256 CUs, `fit` of them at a
+// time on one, in passes of one wavefront: each batch takes as long as its busiest SIMD.
+// Workgroups that share a CU overlap a little; a lone wavefront on a SIMD waits more.
+double passes(long groups, int fit, int w) {
+  auto batch = [&](int r) {
+    const double b = std::max((double)((w * r + 3) / 4), 0.85 * r * ((w + 3) / 4));
+    return r == 0 ? 0.0 : std::max(b, 1.25);
+  };
+  const int r = (int)((groups + 255) / 256);
+  return (r / fit) * batch(fit) + batch(r % fit);
+}
+}  // namespace
+
+// Against k_taylor_g, whose workgroup is one block's row tiles: the time of each from its
+// products a wavefront (the padding of N to 16 and of the contraction index is its loss) and
+// the passes that its workgroups take.  This one has fewer and longer wavefronts, so that it
+// is for calls that fill the chip: M = 72, N = 18, walker moves, k_taylor_g and here, 100
+// walkers 154 and 182 us, 140 271 and 189, 500 518 and 294; M = 128, N = 20, 100 walkers 243
+// and 428, 300 626 and 824; M = 142, N = 35, 20 walkers 545 and 373, 300 1684 and 1150.  Over
+// 220 sizes the choice is 0.2 % behind the better one in the mean (the products alone, for calls
+// of 256 wavefronts or more: 5 %).  Both give the same bits, so that a walker does not depend on
+// how many others share the call.
 bool taylor_q_better(const afqmc_ctx_s* c, int n, int spins) {
-  const long nct = (spins * c->N + 7) / 8, ntc = (c->N + 15) / 16;
-  const long here = nct * 2 * (4 * ((c->M + 3) / 4)), there = (long)spins * ntc * 4 * c->MT;
-  return 100 * there >= 115 * here && n * nct >= 256;
+  const int KT = c->MT / 16, KS = (c->M + 3) / 4, ntc = (c->N + 15) / 16;
+  const q_shape q(c->N, spins);
+  const int waves = KT <= 5 ? 16 : KT <= 7 ? 12 : 8;  // by registers, of this kernel on a CU
+  const int fit = std::max(1, std::min(waves / q.nwv, (160 * 1024) / (2 * panel_size(c->M) * 16)));
+  const double here = 2.0 * KT * KS * passes((long)n * q.parts, fit, q.active);
+  const double there = 16.0 * ntc * KT * passes((long)n * spins, KT <= 4 ? 2 : 1, KT);
+  return there >= 1.1 * here;
 }
 
 hipError_t launch_taylor_q(const afqmc_ctx_s* c, int n, int spins, int n_taylor,

@@ -44,10 +44,12 @@ def same(big, small, n):
         assert torch.equal(a[:n], b[:n])
 
 
-# (M, N, walkers, of the small call): row tiles that end on, before and past a multiple of
-# 16, one to three column tiles, one to several workgroups a V
-MOVES = [(66, 3, 300, 5), (72, 18, 60, 7), (81, 21, 45, 1), (96, 24, 50, 3), (128, 8, 140, 30),
-         (142, 35, 40, 2), (160, 40, 30, 3)]
+# (M, N, walkers, of the small call): the two calls of a pair run different kernels (at 81 and
+# 128 orbitals the same one); 3 to 10 row tiles, one to three column tiles, one to several
+# workgroups a V
+MOVES = [(40, 18, 140, 7), (50, 20, 140, 5), (66, 3, 300, 5), (72, 18, 140, 7), (81, 21, 45, 1),
+         (96, 24, 140, 3), (100, 25, 140, 4), (112, 28, 140, 3), (128, 8, 140, 30),
+         (137, 19, 140, 30), (142, 35, 100, 40), (160, 40, 100, 3)]
 
 
 @pytest.mark.parametrize("shape", MOVES)
@@ -90,7 +92,7 @@ def test_trial_slices(shape):
     same(*out, few)
 
 
-@pytest.mark.parametrize("shape", [(33, 17, 24, 2, 5), (66, 5, 40, 3, 12)])
+@pytest.mark.parametrize("shape", [(33, 17, 24, 2, 5), (66, 5, 40, 3, 12), (125, 4, 140, 3, 4)])
 def test_back_propagation(shape):
     M, N, many, few, P = shape
     say("back-propagation", shape)
