@@ -103,6 +103,17 @@ def measured_traffic(workload):
     return nbytes if ok else None
 
 
+def contraction_kernel(M, N, precision, complex_trial=False):
+    """The kernel that afqmc_local_energy's contraction runs (afqmc_api.hip,
+    contraction_kernels; contract_in_registers in k_contract.hip)."""
+    if precision == 0:
+        one_wave = M <= 64 and 12 < N <= 16 and M > (M + 15) // 16 * 16 - 8
+        return "k_contract" if one_wave and not complex_trial else "k_contract_q"
+    if complex_trial:
+        return "k_contract_g"
+    return "k_contract_f32" if precision == 1 else "k_contract_sh"
+
+
 def contraction_flops(M, N, G, complex_trial=False):
     """Algorithmic flops of the contraction per (walker, path): the real
     half-rotation Phi_T^T L_g (2 N M^2), its product with both spins' Theta
@@ -750,11 +761,7 @@ def main():
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak,
                      "unit": "TFLOP/s", "frac": achieved / peak,
                      "traffic": measured_traffic(args.workload),
-                     "kernel": ("k_contract" if sys_.M <= 64 and sys_.N <= 16 and precision == 0
-                                and not ctx.ctrial else
-                                "k_contract_f32" if precision == 1 and not ctx.ctrial else
-                                "k_contract_sh" if precision in (2, 3)
-                                else "k_contract_q")
+                     "kernel": contraction_kernel(sys_.M, sys_.N, precision, ctx.ctrial)
                                + (" (complex trial)" if ctx.ctrial else "")
                                + " (+ k_combine) in afqmc_local_energy",
                      "ms_per_launch": contract_ms, "flops_per_launch": flops},

@@ -1,7 +1,7 @@
 // Back-propagated one-body density matrix (App. B, Measurement; Eqs.
 // AFQMC_Metropolis_measure and AFQMC_Metropolis_measure2).  The projectors of
-// the restored steps reuse the propagator's kernels (k_vbuild and k_taylor_g
-// with one block per path, the walker's V shared by its paths); the overlap
+// the restored steps reuse the propagator's kernels (k_vbuild, and k_taylor_g or
+// k_taylor_q with one block per path, the walker's V shared by its paths); the overlap
 // with the saved walker reuses the complex-trial overlap kernel.  Here: the
 // field history, and the path-weighted density per walker and its weighted
 // sum over walkers.

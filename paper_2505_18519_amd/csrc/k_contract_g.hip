@@ -1,5 +1,5 @@
 // Cholesky-vector contraction of complex (multi-slice) trials with FP32 matrix-core
-// products (real trials with FP32 products run k_contract_sh, FP64 contexts
+// products (real trials with FP32 products run k_contract_f32, FP64 contexts
 // k_contract and k_contract_q).  Same
 // quantities as k_contract (Sec. III.A, Eq. local-obs; Eq. shift1):
 //   Y_g = Phi_T^T L_g,  f_g^s = Y_g Theta^s,  vb_g = sum_s tr f_g^s,
