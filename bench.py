@@ -54,8 +54,8 @@ WORKLOADS = {
 # the plain-copy calibration (profiles/traffic_k_contract_*.md), valid while the
 # kernel source is the one measured: workload -> (source file, sha256 prefix, bytes)
 TRAFFIC = {
-    "fp64": ("k_contract.hip", "3e530ceca57bbae8", 454532096),
-    "fp64-prior": ("k_contract.hip", "3e530ceca57bbae8", 454532096),
+    "fp64": ("k_contract.hip", "525d17276f09c93e", 454525952),
+    "fp64-prior": ("k_contract.hip", "525d17276f09c93e", 454525952),
 }
 
 # Proposal of each per-step workload: the default FP64 leg runs the random walk

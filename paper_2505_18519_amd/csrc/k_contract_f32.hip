@@ -31,10 +31,10 @@
 // Measured, before (one path and vector at a time, L through LDS, three
 // wavefronts a path) and now: M = 96, N = 24, 384 vectors, 8192 paths 30.8 -> 21.9 ms
 // (90 -> 127 TFLOP/s of unpadded products; a large FP32 matrix product reaches 153);
-// M = 64, 256 vectors, 4096 paths: N = 8 2.68 -> 1.02 ms, N = 16 2.56 -> 2.36, N = 24
-// 6.03 -> 4.45; M = 128, N = 16, 2048 paths 4.68 -> 3.49; N = 32, 512 vectors, 4096
-// paths 33.3 -> 33.5.  With few paths the vectors are split over workgroups: M = 70,
-// N = 22, 240 vectors, 40 paths 1.79 -> 0.13 ms.
+// M = 64, 256 vectors, 4096 paths: N = 8 2.68 -> 0.99 ms, N = 16 2.56 -> 2.22, N = 24
+// 6.03 -> 4.35; M = 128, N = 16, 2048 paths 4.68 -> 3.49; N = 32, 512 vectors, 4096
+// paths 33.3 -> 33.3.  With few paths the vectors are split over workgroups: M = 70,
+// N = 22, 240 vectors, 40 paths 1.79 -> 0.14 ms.
 #include "afqmc_internal.h"
 #include "contract_sum.h"
 #include "dev_common.h"
@@ -321,7 +321,7 @@ static int tiles(const afqmc_ctx_s* c) {
 
 // Ranges of g (slots: one workgroup a CU, or three of the small ones of N <= 8; at least
 // eight groups of vectors to a range).  256 paths of M = 96, N = 24 (64 workgroups): 2.8 ms in
-// one range, 0.81 in six.
+// one range, 0.72 in four.
 contract_plan contract_f32_plan(const afqmc_ctx_s* c, int nw) {
   const int T = tiles(c), pp = T == 4 ? 2 : 4;
   const int ngrp = (c->G + 2) / 2;

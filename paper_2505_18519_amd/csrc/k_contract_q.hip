@@ -24,10 +24,10 @@
 // operand then feeds both paths.  A few paths (or a last round of workgroups that fills
 // little of the chip) are split further over ranges of g (contract_q_plan).
 //
-// Measured on 2048 (or as many as fill the chip) paths, before (operands in registers,
-// or for N > 32 streamed, N padded to 16) and now, TFLOP/s of the unpadded products:
-// M = 24, N = 6: 7.7 -> 16.7; 45, 11: 18 -> 29; 72, 18: 15 -> 41; 96, 24: 34 -> 58;
-// 128, 16: 42 -> 56; 112, 28: 45 -> 59; 142, 35: 18 -> 54; 160, 40: 31 -> 58; 128, 32:
+// Measured on 2048 paths (M > 128: 1024), before (operands in registers, or for N > 32
+// streamed, N padded to 16) and now, TFLOP/s of the unpadded products:
+// M = 24, N = 6: 7.7 -> 18.7; 45, 11: 18 -> 36; 72, 18: 15 -> 46; 96, 24: 34 -> 58;
+// 128, 16: 42 -> 61; 112, 28: 45 -> 56; 142, 35: 18 -> 55; 160, 40: 31 -> 58; 128, 32:
 // 60 -> 60.
 #include "afqmc_internal.h"
 #include "contract_sum.h"

@@ -604,8 +604,8 @@ __global__ void k_to_bf16_op(size_t n, int MT, const double* __restrict__ src,
 
 // Ranges of g, for calls that do not fill one round of the chip (eight wavefronts a CU), at
 // least two steps of BFL vectors to a range.  40 paths of M = 96, N = 24, 384 vectors: BF16
-// 0.80 -> 0.083 ms, split BF16 1.64 -> 0.155; 200 paths of M = 80, N = 26: 0.30 -> 0.18 and
-// 0.79 -> 0.37.  Past one round a split gained little (2 % at 1.2 rounds) or lost (9 % at
+// 0.80 -> 0.073 ms, split BF16 1.64 -> 0.119; 200 paths of M = 80, N = 26: 0.30 -> 0.13 and
+// 0.79 -> 0.27.  Past one round a split gained little (2 % at 1.2 rounds) or lost (9 % at
 // 5.5 rounds).
 contract_plan contract_sh_plan(const afqmc_ctx_s* c, int nw) {
   const int ncp = (2 * c->N + 15) / 16;
